@@ -471,49 +471,78 @@ __global__ __launch_bounds__(NW * kWave, 8 / NW) void k_dist_packed(DistArgs a, 
     }
 }
 
-// The packed copy.  Thread i writes 16-byte chunk i of the fragments: chunk
-// (b * d / 32 + c) * 64 + l is row 16 b + l % 16, elements 32 c + 8 (l / 16) .. +8
-// of the row-major keys (zeros for rows past n), at byte (c * 64 + l) * 16 of
-// block b.
-__global__ __launch_bounds__(256) void k_pack_fragments(const u32x4_t *keys, int64_t n, int64_t d, char *packed,
-                                                        int64_t chunks) {
-    const int64_t steps = d / 32;      // 32-element steps per row
-    const int64_t row_chunks = d / 8;  // 16-byte chunks per row
-    const int64_t bb = packed_block_bytes(d);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < chunks;
-         i += static_cast<int64_t>(gridDim.x) * 256) {
-        const int64_t l = i & 63, bc = i >> 6;
-        const int64_t b = bc / steps, c = bc - b * steps;
-        const int64_t row = b * kBlockRows + (l & 15);
-        const u32x4_t zero = {0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4_t *>(packed + b * bb + (c * 64 + l) * 16) =
-            row < n ? keys[row * row_chunks + c * 4 + (l >> 4)] : zero;
+// The packed copy: one workgroup of NW waves per block of 16 rows, each wave
+// kPackSteps consecutive 32-element steps of d at a time.  In step c lane l
+// loads the 16 bytes of row 16 b + l % 16, elements 32 c + 8 (l / 16) .. +8
+// (zeros for rows past n) and stores them at byte (c * 64 + l) * 16 of block b,
+// a KiB a step; the squares of the same registers give ||k||^2, so the keys are
+// read once for both.  The norm is summed in the matrix-core kernels' order:
+// each lane its fragments' words in step order (dot2), then (g0 + g1) + (g2 +
+// g3) over the lane groups; a lane's sum is a chain over the steps, so the
+// waves add their steps in turn, through LDS.
+//
+// Bound: HBM, one read and one write of the store.  A block's rows are read,
+// and its KiB written, all at once: with one wave walking a whole block
+// (16 row streams of 64 bytes a step per wave, all the chip's waves apart) the
+// same bytes moved at 4.6 TB/s against 5.5 TB/s (65,521 rows of d = 4096:
+// 230 us against 193 us; a fragment pass and a norm pass took 370 us).  The
+// loads are cached (both 64-byte halves of a line are used, by two steps;
+// non-temporal they cost 20%), the stores are not.
+constexpr int kPackSteps = 16;
+
+template <knn_dtype DT, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_pack(const u32x4_t *keys, int64_t n, int64_t d, char *packed) {
+    __shared__ float part[kWave];  // each lane's sum so far
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+    const int64_t b = blockIdx.x;
+    const int steps = static_cast<int>(d / 32);
+    const int64_t row = b * kBlockRows + (lane & 15);
+    const bool in = row < n;
+    // rows past n read the block's first row
+    const u32x4_t *src = keys + (in ? row : b * kBlockRows) * (d / 8) + (lane >> 4);
+    char *blk = packed + b * packed_block_bytes(d);
+    u32x4_t *dst = reinterpret_cast<u32x4_t *>(blk) + lane;
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
+    if (wave == 0) part[lane] = 0.0f;
+    for (int base = 0; base < steps; base += NW * kPackSteps) {
+        const int c0 = base + wave * kPackSteps;
+        u32x4_t v[kPackSteps];
+#pragma unroll
+        for (int u = 0; u < kPackSteps; ++u) v[u] = src[4 * (c0 + u < steps ? c0 + u : steps - 1)];
+#pragma unroll
+        for (int u = 0; u < kPackSteps; ++u) {
+            v[u] = in && c0 + u < steps ? v[u] : zero;
+            if (c0 + u < steps) __builtin_nontemporal_store(v[u], dst + 64 * (c0 + u));
+        }
+        for (int w = 0; w < NW; ++w) {
+            // wave w - 1's sums are in LDS; a bare barrier, since a fenced one would wait for the stores
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (w == wave) {
+                float p = part[lane];
+#pragma unroll
+                for (int u = 0; u < kPackSteps; ++u) p = dot_vec<DT>(v[u], p);  // steps past the end add zeros
+                part[lane] = p;
+            }
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const float s = group4_sum(part[lane]);
+        if (lane < kBlockRows) reinterpret_cast<float *>(blk + 32 * d)[lane] = s;
     }
 }
 
-// ||k||^2 of every row into its block, in the matrix-core kernels' order:
-// four threads per row, thread g summing the words of elements 32 c + 8 g .. +8
-// for c = 0, 1, ... (dot2), then (g0 + g1) + (g2 + g3).  Rows past n get 0.
 template <knn_dtype DT>
-__global__ __launch_bounds__(256) void k_pack_norms(const u32x4_t *keys, int64_t n, int64_t d, char *packed,
-                                                    int64_t rows) {
-    const int64_t steps = d / 32;
-    const int64_t row_chunks = d / 8;
-    const int64_t bb = packed_block_bytes(d);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < 4 * rows;
-         i += static_cast<int64_t>(gridDim.x) * 256) {
-        const int64_t row = i >> 2;
-        const int g = static_cast<int>(i & 3);
-        float p = 0.0f;
-        if (row < n) {
-            const u32x4_t *kr = keys + row * row_chunks + g;
-            for (int64_t c = 0; c < steps; ++c) p = dot_vec<DT>(kr[4 * c], p);
-        }
-        p += __shfl_xor(p, 1);  // g0 + g1, g2 + g3 (the grid covers whole waves: every lane takes part)
-        p += __shfl_xor(p, 2);  // (g0 + g1) + (g2 + g3)
-        if (g == 0 && row < rows)
-            reinterpret_cast<float *>(packed + (row / kBlockRows) * bb + 32 * d)[row % kBlockRows] = p;
-    }
+void launch_pack(const u32x4_t *keys, int64_t n, int64_t d, char *packed, int64_t nblk, hipStream_t st) {
+    const dim3 grid(static_cast<unsigned>(nblk));
+    const int64_t waves = d / (32 * kPackSteps);  // as many as have whole steps to do
+    if (waves >= 8) hipLaunchKernelGGL((k_pack<DT, 8>), grid, dim3(8 * kWave), 0, st, keys, n, d, packed);
+    else if (waves >= 4) hipLaunchKernelGGL((k_pack<DT, 4>), grid, dim3(4 * kWave), 0, st, keys, n, d, packed);
+    else if (waves >= 2) hipLaunchKernelGGL((k_pack<DT, 2>), grid, dim3(2 * kWave), 0, st, keys, n, d, packed);
+    else hipLaunchKernelGGL((k_pack<DT, 1>), grid, dim3(kWave), 0, st, keys, n, d, packed);
 }
 
 // Ring depth NS of each group size, used when NS divides the steps per pass
@@ -597,23 +626,12 @@ int64_t packed_key_bytes(int64_t n, int64_t d) { return (n + kBlockRows - 1) / k
 hipError_t launch_pack_keys(const void *keys, int64_t n, int64_t d, knn_dtype dtype, void *packed,
                             hipStream_t stream) {
     const int64_t nblk = (n + kBlockRows - 1) / kBlockRows;
-    const int64_t chunks = nblk * kBlockRows * d / 8;
-    if (chunks == 0) return hipSuccess;
-    int64_t blocks = (chunks + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
+    if (nblk == 0) return hipSuccess;
+    if (nblk > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const u32x4_t *k = static_cast<const u32x4_t *>(keys);
     char *out = static_cast<char *>(packed);
-    hipLaunchKernelGGL(k_pack_fragments, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, k, n, d, out,
-                       chunks);
-    const int64_t rows = nblk * kBlockRows;
-    int64_t nb = (4 * rows + 255) / 256;
-    if (nb > 4096) nb = 4096;
-    if (dtype == KNN_BF16)
-        hipLaunchKernelGGL(k_pack_norms<KNN_BF16>, dim3(static_cast<unsigned>(nb)), dim3(256), 0, stream, k, n, d, out,
-                           rows);
-    else
-        hipLaunchKernelGGL(k_pack_norms<KNN_F16>, dim3(static_cast<unsigned>(nb)), dim3(256), 0, stream, k, n, d, out,
-                           rows);
+    if (dtype == KNN_BF16) launch_pack<KNN_BF16>(k, n, d, out, nblk, stream);
+    else launch_pack<KNN_F16>(k, n, d, out, nblk, stream);
     return hipGetLastError();
 }
 

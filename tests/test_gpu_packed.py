@@ -79,6 +79,24 @@ def test_pack_layout(dtype, n, d):
     np.testing.assert_allclose(nr[:n].astype(np.float64), ref, rtol=2e-6, atol=0)
 
 
+# d over the workgroup sizes of the pack kernel (1, 2, 4 and 8 waves of sixteen 32-element steps), whole and
+# with a remainder, and rows that leave the last block partly filled.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n,d", [(17, 512), (31, 896), (15, 1024), (33, 1152), (18, 2048), (47, 3968), (31, 4096),
+                                 (49, 5248), (16, 8192)])
+def test_pack_wave_splits(dtype, n, d):
+    _say(f"pack wave splits {dtype} n={n} d={d}")
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    k = (torch.randn((n, d), generator=g, device="cuda") * (8 / math.sqrt(d))).to(dtype)
+    keys, norms = _unpack(knn.pack_keys(k), n, d)
+    np.testing.assert_array_equal(keys[:n], k.view(torch.int16).cpu().numpy().view(np.uint16))
+    assert not keys[n:].any() and not norms[n:].any()
+    # the row-major matrix-core kernel's distances of a zero query are its norms: the same sums, bit for bit
+    off = torch.tensor([0, n], device="cuda")
+    d0 = knn.distances(torch.zeros(16, d, dtype=dtype, device="cuda"), k, off, torch.tensor([0, 16], device="cuda"))
+    np.testing.assert_array_equal(norms[:n], d0[0].cpu().numpy())
+
+
 # (name, queries per set, key set sizes, d): group sizes 16 (queries from global memory), 32, 64 and 128
 # (queries through the LDS ring), deep rings where 64-element steps per pass are a multiple of the ring depth
 # and two-set rings otherwise, key sets whose rows start inside a 16-row block.
