@@ -2,9 +2,10 @@
 // squared L2 distance whose negative is the similarity s(q, k) of the paper
 // (Section 2.2, sentence after eq. non-parametric; Appendix A).
 //
-// The work is HBM-bound for every batch size this kernel serves (one to eight
-// queries per key set): each key row is read from HBM exactly once and dotted
-// with every query of its set while it sits in registers.
+// The work is HBM-bound for the batches these kernels serve (one to eight
+// queries per key set): each key row is read from HBM once and dotted with the
+// queries of its set while it sits in registers.  Sets whose queries don't fit
+// the registers go to the multi-query kernel (dist_multi.hip).
 //
 // Numerics (shared by the on-the-fly norms here and knn_key_sqnorms): a row is
 // cut into 32-bit words (two bf16/f16 elements or one fp32 element) and
@@ -558,8 +559,8 @@ int dist_tile_rows(int64_t d, knn_dtype dtype, int64_t S, int64_t max_keys, int6
     return static_cast<int>(rpt);
 }
 
-DistPlan plan_distances(int64_t d, knn_dtype dtype, int64_t max_queries, const void *queries,
-                        const void *keys) {
+DistPlan plan_distances(int64_t d, knn_dtype dtype, int64_t S, int64_t max_keys, int64_t max_queries,
+                        const void *queries, const void *keys) {
     DistPlan p{};
     const int vec = vec_elems(dtype);
     p.vec = vector_path_ok(d, dtype, queries, keys);
@@ -580,6 +581,21 @@ DistPlan plan_distances(int64_t d, knn_dtype dtype, int64_t max_queries, const v
         int nq = 8;
         while (nq > 1 && (nq * p.cpl > kQueryRegChunks || nq / 2 >= mq)) nq >>= 1;
         p.nq = nq;
+        // The multi-query kernel (dist_multi.hip) instead, where this one would
+        // read the keys more than once or hold more than four queries, once
+        // there are keys enough to make up for its longer start (about 5 us: it
+        // stages the queries in LDS).  Measured, this kernel / that one: 8 queries of d = 1024, 7,000
+        // keys 9.8 / 12.0 us, 14,000 keys 16.8 / 13.8 us; 15 queries of d = 256,
+        // 3,000 keys (two passes) 9.6 / 11.8 us, 20,000 keys 26.1 / 18.5 us; 4
+        // queries of d = 4096, 7,000 keys (two passes) 22.6 / 19.1 us; in one
+        // pass of four queries this one is ahead (4 x 65,536 keys of d = 2048:
+        // 161 / 170 us).
+        const int64_t passes = (mq + nq - 1) / nq;
+        const int64_t rows = passes * (max_keys < 1 ? 1 : max_keys);  // that one set makes it read
+        if ((passes > 1 || nq > 4) && S >= (kMultiMinRows + rows - 1) / rows) {
+            p.multi = true;
+            p.nq = multi_queries(d, dtype, mq);
+        }
     } else {
         p.cpl = 0;
         int nq = 8;
@@ -598,6 +614,7 @@ hipError_t launch_distances(const DistPlan &plan, knn_dtype dtype, const DistArg
     if (plan.mfma && plan.packed) return launch_distances_packed(plan.mq, dtype, args, S, plan.groups, stream);
     if (plan.mfma) return launch_distances_mfma(plan.mq, dtype, args, S, plan.groups, stream);
     if (plan.packed) return hipErrorInvalidValue;  // packed keys are read by the matrix-core kernels only
+    if (plan.multi) return launch_distances_multi(plan, dtype, args, S, stream);
     const int64_t nblocks = S * plan.tiles_per_set;
     if (nblocks > 0x7fffffffLL || plan.groups > 65535) return hipErrorInvalidConfiguration;
     const dim3 grid(static_cast<unsigned>(nblocks), static_cast<unsigned>(plan.groups));

@@ -165,7 +165,7 @@ knn_status validate_part(const Call &c, int part) {
     if (dist && (!c.queries || !c.keys)) return KNN_ERR_INVALID_ARG;
     if (c.packed) {  // packed keys: 16-bit elements, read by the matrix-core kernels only
         if (c.dtype != KNN_BF16 && c.dtype != KNN_F16) return KNN_ERR_INVALID_ARG;
-        if (dist && !plan_distances(c.d, c.dtype, c.max_queries, c.queries, c.keys).mfma) return KNN_ERR_UNSUPPORTED;
+        if (dist && !plan_distances(c.d, c.dtype, c.S, c.max_keys, c.max_queries, c.queries, c.keys).mfma) return KNN_ERR_UNSUPPORTED;
     }
     if ((sel || mix) && (!c.nbr_ids || !c.nbr_dists)) return KNN_ERR_INVALID_ARG;
     if (mix && (!c.values || !c.p_lm || !c.p_m)) return KNN_ERR_INVALID_ARG;
@@ -259,7 +259,7 @@ knn_status run_part(const Call &c, int part, hipStream_t stream) {
     float *tmin = ws ? reinterpret_cast<float *>(ws + L.off_tmin) : nullptr;
     float *tmax = ws ? reinterpret_cast<float *>(ws + L.off_tmax) : nullptr;
     if (part == KNN_PART_DISTANCES) {
-        DistPlan p = plan_distances(c.d, c.dtype, c.max_queries, c.queries, c.keys);
+        DistPlan p = plan_distances(c.d, c.dtype, c.S, c.max_keys, c.max_queries, c.queries, c.keys);
         p.packed = c.packed;
         p.rows_per_tile = L.rows_per_tile;
         p.tiles_per_set = L.tiles_per_set;
@@ -564,7 +564,7 @@ knn_status knn_distances(const void *queries, const void *keys, const float *key
     if (!valid_dtype(dtype) || ld_out < max_keys_per_set) return KNN_ERR_INVALID_ARG;
     if (packed && dtype != KNN_BF16 && dtype != KNN_F16) return KNN_ERR_INVALID_ARG;
     if (B > 0x7fffffffLL || max_keys_per_set > 0x7fffffffLL || max_queries_per_set > 65535) return KNN_ERR_UNSUPPORTED;
-    DistPlan p = plan_distances(d, dtype, max_queries_per_set, queries, keys);
+    DistPlan p = plan_distances(d, dtype, S, max_keys_per_set, max_queries_per_set, queries, keys);
     if (packed && !p.mfma) return KNN_ERR_UNSUPPORTED;
     p.packed = packed;
     p.rows_per_tile = dist_tile_rows(d, dtype, S, max_keys_per_set, max_queries_per_set);

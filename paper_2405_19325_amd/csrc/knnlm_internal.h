@@ -25,6 +25,7 @@ struct DistPlan {
     bool mfma;              // query batches: q.k on the matrix cores (16-bit elements, >= 16 queries per set)
     bool packed;            // MFMA path: the keys are the packed copy (knn_pack_keys)
     int mq;                 // MFMA path: 16-query blocks per workgroup (1, 2, 4 or 8)
+    bool multi;             // several queries per set on the vector ALUs, from LDS (dist_multi.hip)
     bool vec;               // 16-byte loads (d % VEC == 0, aligned rows) vs element loads
     int cpl;                // chunks per lane (vector path), power of two <= kMaxCplVec
     int nq;                 // queries per workgroup (1, 2, 4 or 8)
@@ -78,8 +79,8 @@ __device__ __forceinline__ bool key_masked(const uint32_t *mask, int64_t g) {
     return ((mask[g >> 5] >> (g & 31)) & 1u) != 0u;
 }
 
-DistPlan plan_distances(int64_t d, knn_dtype dtype, int64_t max_queries, const void *queries,
-                        const void *keys);
+DistPlan plan_distances(int64_t d, knn_dtype dtype, int64_t S, int64_t max_keys, int64_t max_queries,
+                        const void *queries, const void *keys);
 
 // The matrix-core path serves 16-bit keys with d % kMfmaSpan == 0 and
 // d <= kMfmaMaxD when at least kMfmaMinQueries queries share a key set.
@@ -100,6 +101,14 @@ hipError_t launch_distances_mfma(int mq, knn_dtype dtype, const DistArgs &args, 
 // The same stages over keys in the packed layout (mfma_packed.hip).
 hipError_t launch_distances_packed(int mq, knn_dtype dtype, const DistArgs &args, int64_t S, int64_t groups,
                                    hipStream_t stream, int fm = 0);
+// Several queries per set on the vector ALUs (plan.multi): queries per workgroup
+// (a power of two whose rows fit kMultiQueryLds bytes of LDS), workgroups per launch.
+constexpr size_t kMultiQueryLds = 128 * 1024;
+constexpr int64_t kMultiBlocks = 256;
+constexpr int64_t kMultiMinRows = 10000;  // key rows x passes of the streaming kernel from which it is taken
+int multi_queries(int64_t d, knn_dtype dtype, int64_t max_queries);
+hipError_t launch_distances_multi(const DistPlan &plan, knn_dtype dtype, const DistArgs &args, int64_t S,
+                                  hipStream_t stream);
 // Bytes of the packed copy of n rows of d 16-bit elements: blocks of 16 rows
 // (the last one padded), each its fragments and then its rows' ||k||^2.
 int64_t packed_key_bytes(int64_t n, int64_t d);

@@ -31,10 +31,12 @@ constexpr int kVmcntZero = vmcnt_encoding<0>();
 // M0, which the compiler reserves (a clobber of it is ignored): the kernels
 // that use it leave M0 to these loads alone (their assembly sets it nowhere
 // else).
-__device__ __forceinline__ void load_to_lds_16(const void *src, u32x4_t *dst) {
-    const uint32_t lds = __builtin_amdgcn_readfirstlane(
-        static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) u32x4_t *)dst)));
+__device__ __forceinline__ void load_to_lds_16(const void *src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds));
+}
+__device__ __forceinline__ void load_to_lds_16(const void *src, u32x4_t *dst) {
+    load_to_lds_16(src, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(
+                            reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) u32x4_t *)dst)))));
 }
 
 template <knn_dtype DT>
