@@ -54,9 +54,10 @@ bool fused_shape(int64_t B, int64_t d, knn_dtype dtype, int64_t max_queries, int
            select_split_parts(B, ld, r) == 0 && select_wide_parts(B, ld, r, tiles_per_set) > 0;
 }
 
-Layout layout(int64_t B, int64_t d, int64_t S, int64_t max_keys, int64_t max_queries, knn_dtype dtype, int32_t r) {
+Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, knn_dtype dtype, int32_t r,
+                 int rows_per_tile) {
     Layout L{};
-    L.rows_per_tile = dist_tile_rows(d, dtype, S, max_keys, max_queries);
+    L.rows_per_tile = rows_per_tile;
     L.tiles_per_set = (max_keys + L.rows_per_tile - 1) / L.rows_per_tile;
     if (L.tiles_per_set < 1) L.tiles_per_set = 1;
     L.ld = L.tiles_per_set * L.rows_per_tile;
@@ -88,6 +89,23 @@ Layout layout(int64_t B, int64_t d, int64_t S, int64_t max_keys, int64_t max_que
     return L;
 }
 
+// The layout of a call.  Query batches on row-major keys take finer tiles where
+// the launch would leave CUs idle (mfma_fine_rows), except where the fused
+// select runs (its sample is laid out in whole tiles) and where the finer
+// tiles' extrema, a few percent of the workspace, would be what does not fit
+// the static scratch array.
+Layout layout(int64_t B, int64_t d, int64_t S, int64_t max_keys, int64_t max_queries, knn_dtype dtype, bool packed,
+              int32_t r) {
+    const int rows = dist_tile_rows(d, dtype, S, max_keys, max_queries);
+    const Layout L = layout_of(B, d, max_keys, max_queries, dtype, r, rows);
+    if (packed || L.fused || !mfma_shape(d, dtype, max_queries)) return L;
+    const int fine = mfma_fine_rows(rows, S, max_keys, max_queries);
+    if (fine == rows) return L;
+    const Layout F = layout_of(B, d, max_keys, max_queries, dtype, r, fine);
+    constexpr size_t scratch_bytes = KNNLM_NOALLOC_SCRATCH_BYTES;
+    return F.total > scratch_bytes && L.total <= scratch_bytes ? L : F;
+}
+
 bool finite_pos(float x) { return isfinite(x) && x > 0.0f; }
 
 knn_status check_sizes(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total_keys,
@@ -104,7 +122,7 @@ knn_status check_sizes(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total
     if (need_vocab && V > 0x7fffffffLL) return KNN_ERR_UNSUPPORTED;
     if (d > (int64_t(1) << 40) / elem_bytes(dtype)) return KNN_ERR_UNSUPPORTED;
     if (r > min_keys) return KNN_ERR_R_EXCEEDS_N;
-    const Layout L = layout(B, d, S, max_keys, max_queries, dtype, r);
+    const Layout L = layout(B, d, S, max_keys, max_queries, dtype, false, r);
     if (S * L.tiles_per_set > 0x7fffffffLL) return KNN_ERR_UNSUPPORTED;
     if (max_queries > 65535) return KNN_ERR_UNSUPPORTED;  // query groups per set on grid.y
     return KNN_OK;
@@ -179,7 +197,7 @@ knn_status validate_part(const Call &c, int part) {
     if (dist || sel) {
         if (!c.workspace) return KNN_ERR_WORKSPACE;
         if (reinterpret_cast<uintptr_t>(c.workspace) % kAlign) return KNN_ERR_WORKSPACE;
-        const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.r);
+        const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r);
         if (c.workspace_bytes < L.total) return KNN_ERR_WORKSPACE;
     }
     return KNN_OK;
@@ -253,7 +271,7 @@ FusedArgs fused_args(const Layout &L, char *ws) {
 }
 
 knn_status run_part(const Call &c, int part, hipStream_t stream) {
-    const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.r);
+    const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r);
     char *ws = static_cast<char *>(c.workspace);
     float *dist = ws ? reinterpret_cast<float *>(ws + L.off_dist) : nullptr;
     float *tmin = ws ? reinterpret_cast<float *>(ws + L.off_tmin) : nullptr;
@@ -433,7 +451,7 @@ knn_status knn_lm_mixture_noalloc(const void *queries, const void *keys, const f
     knn_status st = check_sizes(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set, max_queries_per_set,
                                 base_dtype(dtype), r, true);
     if (st != KNN_OK) return st;
-    const size_t need = layout(B, d, S, max_keys_per_set, max_queries_per_set, base_dtype(dtype), r).total;
+    const size_t need = layout(B, d, S, max_keys_per_set, max_queries_per_set, base_dtype(dtype), packed_flag(dtype), r).total;
     if (need > static_cast<size_t>(KNNLM_NOALLOC_SCRATCH_BYTES)) return KNN_ERR_WORKSPACE;
     void *ws = nullptr;
     if ((st = scratch_of_current_device(&ws)) != KNN_OK) return st;
@@ -532,7 +550,10 @@ size_t knn_lm_mixture_workspace_size(int64_t B, int64_t d, int64_t V, int64_t S,
     if (check_sizes(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, r,
                     true) != KNN_OK)
         return 0;
-    return layout(B, d, S, max_keys_per_set, max_queries_per_set, et, r).total;
+    // one size for the call on packed and on row-major keys
+    const size_t row_major = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, false, r).total;
+    const size_t packed = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, true, r).total;
+    return row_major > packed ? row_major : packed;
 }
 
 knn_status knn_lm_mixture_validate(const void *queries, const void *keys, const int32_t *values,
@@ -568,6 +589,7 @@ knn_status knn_distances(const void *queries, const void *keys, const float *key
     if (packed && !p.mfma) return KNN_ERR_UNSUPPORTED;
     p.packed = packed;
     p.rows_per_tile = dist_tile_rows(d, dtype, S, max_keys_per_set, max_queries_per_set);
+    if (p.mfma && !packed) p.rows_per_tile = mfma_fine_rows(p.rows_per_tile, S, max_keys_per_set, max_queries_per_set);
     p.tiles_per_set = (max_keys_per_set + p.rows_per_tile - 1) / p.rows_per_tile;
     if (S * p.tiles_per_set > 0x7fffffffLL || p.groups > 65535) return KNN_ERR_UNSUPPORTED;
     DistArgs a{};

@@ -89,6 +89,7 @@ constexpr int kMfmaSpan = 128;
 constexpr int64_t kMfmaMaxD = 65536;  // a 4096-row tile stays under 2^31 bytes
 bool mfma_shape(int64_t d, knn_dtype dtype, int64_t max_queries);
 int mfma_tile_rows(int64_t d);
+int mfma_fine_rows(int rows, int64_t S, int64_t max_keys, int64_t max_queries);
 int dist_tile_rows(int64_t d, knn_dtype dtype, int64_t S, int64_t max_keys, int64_t max_queries);
 
 hipError_t launch_distances(const DistPlan &plan, knn_dtype dtype, const DistArgs &args, int64_t S,

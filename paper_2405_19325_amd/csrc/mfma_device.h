@@ -21,6 +21,7 @@ constexpr int vmcnt_encoding() {
     return (N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8);
 }
 constexpr int kVmcntZero = vmcnt_encoding<0>();
+constexpr int kLgkmcntAny = 15 << 8;  // taken out of an encoding: wait for every LDS and scalar access as well
 
 // One 16-byte global load per lane straight into LDS: lane l's 16 bytes land at
 // dst + l (dst is the wave's, the same in every lane).  Written as assembly so
@@ -31,12 +32,26 @@ constexpr int kVmcntZero = vmcnt_encoding<0>();
 // M0, which the compiler reserves (a clobber of it is ignored): the kernels
 // that use it leave M0 to these loads alone (their assembly sets it nowhere
 // else).
+// The instruction after the write of M0 may not use it (one wait state).
 __device__ __forceinline__ void load_to_lds_16(const void *src, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds));
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds));
+}
+// The same from a base every lane shares plus 32-bit offsets.
+__device__ __forceinline__ void load_to_lds_16(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds));
+}
+// ... and streamed past the caches, like every key byte that is read once.
+__device__ __forceinline__ void load_to_lds_16_nt(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds));
 }
 __device__ __forceinline__ void load_to_lds_16(const void *src, u32x4_t *dst) {
     load_to_lds_16(src, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(
                             reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) u32x4_t *)dst)))));
+}
+
+// Byte offset in LDS of a pointer into it.
+__device__ __forceinline__ uint32_t lds_offset(const u32x4_t *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) u32x4_t *)p));
 }
 
 template <knn_dtype DT>

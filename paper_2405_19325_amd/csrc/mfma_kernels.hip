@@ -7,26 +7,32 @@
 // products form a dense [queries x d] . [d x keys] contraction: every key
 // element is used by up to 128 queries, so streaming the keys from HBM once
 // needs up to 128 flop per byte -- beyond the vector ALUs, within the
-// matrix cores.  A workgroup of 4 waves takes passes of 128 keys of one set
-// (two blocks of 16 per wave) against up to 128 of the set's queries (MQ
-// blocks of 16), walking d in spans of 128 elements (256 bytes of a row).
+// matrix cores.  A workgroup takes passes of PK keys of one set against up to
+// 128 of the set's queries (MQ blocks of 16), walking d in steps of SPAN
+// elements.
 //
-// Each span of the pass's keys and queries goes HBM -> registers -> LDS -> the
-// matrix cores.  The global loads are coalesced: 16 lanes read one row's
-// 256-byte span, a wave instruction four whole rows.  The LDS copy is
-// swizzled -- chunk c (16 bytes) of row n sits at slot n * 16 + (c ^ (n % 16))
-// -- so that both the row-wise writes and the fragment reads (lane l reads
-// row l % 16, chunk 4 * step + l / 16) touch every bank once.  In MFMA step c
-// lane l holds key (or query) row l % 16 and elements 32c + 8 (l / 16) .. +8
-// of the span -- the same elements for both operands, so the contraction is
-// exact up to fp32 rounding -- for v_mfma_f32_16x16x32 (bf16 or f16, fp32
-// accumulate).  Two LDS buffers alternate: while the matrix cores work on
-// span t, span t + 1 is written to the other buffer, and the next NS spans
-// load into NS register sets (NS = 2 to 4, as many as the shape's registers
-// allow at two waves per SIMD).  The loads are never guarded by a
-// branch, since a branch around loads makes the compiler wait for every load
-// in flight: rows past the data read the tile's first row, and steps past the
-// tile's end re-read its last span (from L2).
+// Bound: HBM.  Each step's keys and queries go straight from HBM (L2 for the
+// queries) to LDS -- 16 bytes a lane, whole 128- or 256-byte pieces of a row,
+// no registers in between -- into a ring of NB span buffers, NB - 1 steps
+// ahead, and one barrier a step orders the buffers.  With the spans staged
+// through registers (two LDS buffers, two to four register sets) a 35-query
+// workgroup ran one wave per SIMD, 98 KiB of LDS and 1.9 us a step; 48 to 72 KiB and
+// 60 to 130 registers let two or three workgroups share a CU.  Measured, before
+// and after, bf16 keys of d = 4096: 8 x 65,536 keys, 16 / 32 / 64 queries 792 / 915 /
+// 1,080 us and 746 / 804 / 905 us (5.75 / 5.35 / 4.75 TB/s); 128 queries on 4 x
+// 65,536 keys of d = 2048: 311 and 306 us.  What is left is the access pattern:
+// 128 bytes of each row at a time stream below the whole-row kernels' 7 TB/s.
+//
+// The LDS copy is swizzled -- chunk c (16 bytes) of row n sits at slot n * CH +
+// (c ^ (n % CH)), CH the chunks of a row's span -- so that the fragment reads
+// (lane l reads row l % 16, chunk 4 * step + l / 16) touch every bank once; the
+// loads' lanes pick their chunks accordingly.  In MFMA step c lane l holds key
+// (or query) row l % 16 and elements 32c + 8 (l / 16) .. +8 of the span -- the
+// same elements for both operands, so the contraction is exact up to fp32
+// rounding -- for v_mfma_f32_16x16x32 (bf16 or f16, fp32 accumulate).  The
+// steps run in the same k order whatever the variant, so the sums are the
+// same.  Rows past the data read the tile's last row, and steps past the tile's
+// end read on in its last pass's rows.
 #include "knnlm_internal.h"
 #include "mfma_device.h"
 
@@ -34,22 +40,18 @@ namespace knnlm {
 
 namespace {
 
-constexpr int kTileQuantum = 256;  // tile rows are multiples of the largest pass (256 keys)
+constexpr int kTileQuantum = 128;  // tile rows: a multiple of the largest pass, or 64 or 32
 
 // Where the epilogue stores the (discarded) distances of rows past the tile or
 // query slots past the group: one word per device, written, never read.
 __device__ float g_mfma_sink;
 
-constexpr int kSpan = kMfmaSpan;  // d is a multiple of this (the largest span)
+constexpr int kSpan = kMfmaSpan;    // d is a multiple of this
 
 // MQ: 16-query blocks per workgroup; WK x WQ waves: WK groups split the
 // pass's PK / 16 key blocks, WQ groups split the query blocks (MQ / WQ each);
-// NS: register sets of prefetched spans (NS spans in flight); NORMS: ||k||^2
-// comes precomputed; PK keys per pass and SPAN elements of d per pipeline
-// step.  A wide query block re-stages its span in LDS once per pass, so
-// 128-query workgroups take 256-key passes of 64-element spans (the same
-// matrix-core work per step as 128 keys x 128 elements, with a quarter less
-// loaded and written to LDS per step, a third less read from it).
+// NB: span buffers (NB - 1 spans in flight); NORMS: ||k||^2 comes precomputed;
+// PK keys per pass and SPAN elements of d per pipeline step.
 //
 // FM (the fused select of query batches on long rows): 0 every tile, the
 // distances written; 1 only the sample pieces (the first sample_rows rows of
@@ -58,23 +60,25 @@ constexpr int kSpan = kMfmaSpan;  // d is a multiple of this (the largest span)
 // whose distance bits are below the query's threshold -- are staged in LDS
 // and appended to the query's list once the tile is done (the list's count is
 // true even past its capacity; a full LDS stage sets the fallback word).
-template <knn_dtype DT, int MQ, int WK, int WQ, int NS, bool NORMS, int PK, int SPAN, int FM = 0>
-__global__ __launch_bounds__(WK * WQ * kWave, 1) void k_dist_mfma(DistArgs a, int64_t n_tiles, int64_t groups) {
+template <knn_dtype DT, int MQ, int WK, int WQ, int NB, bool NORMS, int PK, int SPAN, int FM = 0>
+__global__ __launch_bounds__(WK * WQ * kWave, 2) void k_dist_mfma(DistArgs a, int64_t n_tiles, int64_t groups) {
     constexpr int QW = WQ;
-    constexpr int kChunks = SPAN * 2 / 16;               // 16-byte chunks per row and span
-    constexpr int KSTEPS = SPAN / 32;                    // MFMA steps per span
+    constexpr int kChunks = SPAN * 2 / 16;          // 16-byte chunks per row and step
+    constexpr int KSTEPS = SPAN / 32;               // MFMA steps per span
     constexpr int KBW = PK / 16 / WK;                    // key blocks per wave
-    constexpr int kThreads = WK * WQ * kWave;
+    constexpr int NW = WK * WQ;
+    constexpr int kThreads = NW * kWave;
     constexpr int QB = MQ * 16;
     constexpr int MQW = MQ / QW;                         // query blocks per wave
-    constexpr int KCH = PK * kChunks / kThreads;         // key chunks per thread and step
-    constexpr int QCH = QB * kChunks / kThreads;         // query chunks per thread and step
-    static_assert(MQ % QW == 0 && (PK / 16) % WK == 0 && KCH >= 1 && QCH >= 1, "whole blocks and chunks");
+    constexpr int kRowsPerLoad = kWave / kChunks;        // rows a wave's load covers
+    constexpr int KLD = (PK / kRowsPerLoad + NW - 1) / NW;   // key loads per wave and step
+    constexpr int QLD = (QB / kRowsPerLoad + NW - 1) / NW;   // query loads per wave and step
+    static_assert(MQ % QW == 0 && (PK / 16) % WK == 0, "whole blocks per wave");
     static_assert(SPAN % 32 == 0 && kSpan % SPAN == 0 && kChunks <= 16, "whole MFMA steps, spans dividing d");
     // native 4 x u32 vectors throughout, so that every 16-byte LDS access is
-    // one ds_read_b128 / ds_write_b128 (a struct is split by the compiler)
-    __shared__ __align__(16) u32x4_t klds[2][PK * kChunks];
-    __shared__ __align__(16) u32x4_t qlds[2][QB * kChunks];
+    // one ds_read_b128 (a struct is split by the compiler)
+    __shared__ __align__(16) u32x4_t klds[NB][PK * kChunks];
+    __shared__ __align__(16) u32x4_t qlds[NB][QB * kChunks];
     __shared__ uint32_t smin[QB], smax[QB];
     constexpr int kStage = FM == 2 ? 1024 : 1;  // candidates staged per tile (about 120 at 128 x 4096 keys)
     __shared__ uint64_t stage_key[kStage];
@@ -112,8 +116,9 @@ __global__ __launch_bounds__(WK * WQ * kWave, 1) void k_dist_mfma(DistArgs a, in
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
-    const int wave = (tid / kWave) / QW;  // this wave's group of key blocks
-    const int jq = ((tid / kWave) % QW) * MQW;  // its first query block
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wave = wid / QW;        // this wave's group of key blocks
+    const int jq = (wid % QW) * MQW;  // its first query block
     const int g = lane >> 4, lr = lane & 15;
     const int64_t row_bytes = a.d * 2;
     const int64_t nspan = a.d / SPAN;
@@ -135,50 +140,54 @@ __global__ __launch_bounds__(WK * WQ * kWave, 1) void k_dist_mfma(DistArgs a, in
         thr_l[j] = (FM == 2 && q < nq) ? a.cand_thr[qb + q] : 0u;
     }
 
-    // Loads: chunk i of this thread is row i * R + tid / kChunks of the pass
-    // (keys) or of the query block, 16-byte column tid % kChunks of the span
-    // (R = kThreads / kChunks rows per chunk index, a multiple of 16, so its
-    // LDS slot swz(i * R + rsub, col) is i * R * kChunks + slot0).
-    const int col = tid & (kChunks - 1);
-    const int rsub = tid / kChunks;
-    const int slot0 = swz<kChunks>(rsub, col);
-    constexpr int kRowsPerChunk = kThreads / kChunks;
-    static_assert(kRowsPerChunk % 16 == 0, "the swizzle repeats every 16 rows");
-
-    // Addresses: a uniform base per step plus a 32-bit offset per chunk (a
-    // tile is at most 4096 rows of at most 128 KiB).
-    // NS register sets take the steps in turn, so that NS steps are in flight
-    // while the matrix cores work on another.
-    u32x4_t kr[NS][KCH], qr_[NS][QCH];
-    const char *ktile = kset + r0 * row_bytes;
+    // Loads: a wave's load fills 64 consecutive slots (kRowsPerLoad rows) of a
+    // buffer, each lane with the chunk that the swizzle puts into its slot.
+    // Loads past the pass's (query block's) rows repeat its last.
+    // Addresses: a uniform base per step plus a 32-bit offset per load (a tile
+    // is at most 4096 rows of at most 128 KiB).
+    const int lrow = lane / kChunks;
+    auto lcol = [&](int row) __attribute__((always_inline)) {
+        return static_cast<uint32_t>((lane ^ row) & (kChunks - 1)) * 16u;
+    };
     const uint32_t nrows = static_cast<uint32_t>(r1 - r0);
     const uint32_t rb = static_cast<uint32_t>(row_bytes);
-    uint32_t qoff[QCH];
+    const uint32_t ns = static_cast<uint32_t>(nspan);  // steps fit 32 bits: at most 128 passes of 1024 spans
+    const uint32_t kat = lds_offset(&klds[0][0]), qat = lds_offset(&qlds[0][0]);
+    uint32_t qoff[QLD], qslot[QLD], koff[KLD], kslot[KLD];
 #pragma unroll
-    for (int i = 0; i < QCH; ++i) {
-        const int qrow = i * kRowsPerChunk + rsub;
-        qoff[i] = static_cast<uint32_t>(qrow < nq ? qrow : 0) * rb + static_cast<uint32_t>(col * 16);
+    for (int i = 0; i < QLD; ++i) {
+        const int k = min(wid * QLD + i, QB / kRowsPerLoad - 1);
+        const int row = k * kRowsPerLoad + lrow;
+        qoff[i] = static_cast<uint32_t>(row < nq ? row : 0) * rb + lcol(row);
+        qslot[i] = qat + static_cast<uint32_t>(k) * 1024u;
     }
-    const uint32_t ns = static_cast<uint32_t>(nspan);  // steps fit 32 bits: at most 32 passes of 512 spans
-    auto load = [&](int set, int64_t t) __attribute__((always_inline)) {
-        const uint32_t p = static_cast<uint32_t>(t) / ns, sp = static_cast<uint32_t>(t) - p * ns;
-        const char *kspan = ktile + static_cast<int64_t>(sp) * (2 * SPAN);
-        const char *qspan = qbase + static_cast<int64_t>(sp) * (2 * SPAN);
-        const uint32_t prow = p * PK + static_cast<uint32_t>(rsub);
 #pragma unroll
-        for (int i = 0; i < KCH; ++i) {
-            const uint32_t rr = prow + static_cast<uint32_t>(i * kRowsPerChunk);
-            const uint32_t off = (rr < nrows ? rr : 0u) * rb + static_cast<uint32_t>(col * 16);
-            kr[set][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(kspan + off));
+    for (int i = 0; i < KLD; ++i) kslot[i] = kat + static_cast<uint32_t>(min(wid * KLD + i, PK / kRowsPerLoad - 1)) * 1024u;
+    // the rows of pass p (those past the end read the tile's last row)
+    auto set_pass = [&](uint32_t p) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < KLD; ++i) {
+            const int k = min(wid * KLD + i, PK / kRowsPerLoad - 1);
+            const int row = k * kRowsPerLoad + lrow;
+            koff[i] = min(p * PK + static_cast<uint32_t>(row), nrows - 1u) * rb + lcol(row);
         }
-#pragma unroll
-        for (int i = 0; i < QCH; ++i) qr_[set][i] = *reinterpret_cast<const u32x4_t *>(qspan + qoff[i]);
     };
-    auto write = [&](int set, int buf) __attribute__((always_inline)) {
+    const char *kspan = kset + r0 * row_bytes, *qspan = qbase;  // the next step to load: its span of the rows
+    uint32_t lsp = 0u, lpass = 0u;
+    set_pass(0u);
+    auto load = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < KCH; ++i) klds[buf][i * kRowsPerChunk * kChunks + slot0] = kr[set][i];
+        for (int i = 0; i < KLD; ++i) load_to_lds_16_nt(kspan, koff[i], kslot[i] + static_cast<uint32_t>(buf * PK * kChunks * 16));
 #pragma unroll
-        for (int i = 0; i < QCH; ++i) qlds[buf][i * kRowsPerChunk * kChunks + slot0] = qr_[set][i];
+        for (int i = 0; i < QLD; ++i) load_to_lds_16(qspan, qoff[i], qslot[i] + static_cast<uint32_t>(buf * QB * kChunks * 16));
+        kspan += 2 * SPAN;
+        qspan += 2 * SPAN;
+        if (++lsp == ns) {  // the next pass (past the last one: its rows again)
+            lsp = 0u;
+            kspan -= row_bytes;
+            qspan -= row_bytes;
+            set_pass(++lpass);
+        }
     };
 
     f32x4_t acc[MQW][KBW];
@@ -196,8 +205,7 @@ __global__ __launch_bounds__(WK * WQ * kWave, 1) void k_dist_mfma(DistArgs a, in
     clear();
 
     // The matrix cores over one span in LDS buffer buf (with qn_pass, also
-    // the query norms); the span's MFMA steps unrolled, so that the next
-    // step's fragment reads overlap this step's MFMAs.
+    // the query norms).
     auto compute = [&](int buf, bool qn_pass) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < KSTEPS; ++c) {
@@ -305,37 +313,36 @@ __global__ __launch_bounds__(WK * WQ * kWave, 1) void k_dist_mfma(DistArgs a, in
         clear();
     };
 
-    // Step t: the matrix cores on span t (LDS buffer t % 2); span t + 1 goes
-    // from its register set (t + 1) % NS to the other LDS buffer, and that set
-    // starts loading span t + NS + 1; the barrier orders the LDS buffers
-    // between the waves.  Steps past the tile's last span load that span
-    // again (from L2) and write a buffer no one reads, and the step count is
-    // padded to a multiple of NS with steps whose products are never stored,
-    // so that no branch guards the loads.
-    auto step = [&](int64_t t, int set) __attribute__((always_inline)) {
-        compute(static_cast<int>(t & 1), t < nspan);
-        write(set, static_cast<int>((t + 1) & 1));
-        load(set, t + NS + 1 < T ? t + NS + 1 : T - 1);
-        __syncthreads();
-    };
-    // after step t: the epilogue of its pass when t is the pass's last span (a
-    // padding step is pass npass: rows past r1, nothing is stored)
-    auto pass_end = [&](int64_t t) __attribute__((always_inline)) {
-        const uint32_t p = static_cast<uint32_t>(t) / ns;
-        if (static_cast<uint32_t>(t) - p * ns == ns - 1) epilogue(p);
-    };
-    load(0, 0);
-    write(0, 0);
+    // Step t: once span t is in LDS for every wave (a wave waits for its own
+    // loads of it -- those of the NB - 2 newer steps may still be in flight --
+    // and the barrier for the others'), span t + NB - 1 starts loading into the
+    // buffer that step t - 1 has been read from, and the matrix cores take
+    // span t.  Every step issues the same loads (steps past the tile's last
+    // one load too), so the count in the wait is exact; other memory operations
+    // only make it wait longer.  The step count is padded to a multiple of NB
+    // with steps whose products are never stored.
 #pragma unroll
-    for (int k = 1; k <= NS; ++k) load(k % NS, k < T ? k : T - 1);
-    __syncthreads();
-    for (int64_t t = 0; t < T; t += NS) {
+    for (int k = 0; k < NB - 1; ++k) load(k);
+    uint32_t sp = 0u, pass = 0u;
+    for (int64_t t = 0; t < T; t += NB) {
 #pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            step(t + k, (k + 1) % NS);
-            pass_end(t + k);
+        for (int k = 0; k < NB; ++k) {
+            // (and every LDS access of the steps before is done)
+            __builtin_amdgcn_s_waitcnt(vmcnt_encoding<(NB - 2) * (KLD + QLD)>() & ~kLgkmcntAny);
+            // a bare barrier: a fenced one would wait for every load in flight
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            load((k + NB - 1) % NB);
+            compute(k, pass == 0u);
+            if (++sp == ns) {  // (padding steps may end a pass past the last)
+                sp = 0u;
+                if (pass < static_cast<uint32_t>(npass)) epilogue(pass);
+                ++pass;
+            }
         }
     }
+    __builtin_amdgcn_s_waitcnt(kVmcntZero);  // no load may land in LDS after the workgroup's end
 
     if constexpr (FM == 2) {
         // the staged candidates to their queries' lists (no loads are in flight any more)
@@ -360,26 +367,49 @@ __global__ __launch_bounds__(WK * WQ * kWave, 1) void k_dist_mfma(DistArgs a, in
     }
 }
 
+// The variants: waves, keys per pass, elements per step and span buffers for
+// each group size, for tiles of 32, of 64 and of more rows (one pass a tile for
+// the small ones; then more of d per step, since a step's latency and not its
+// bytes is what takes the time).  Measured on bf16 keys of d = 4096, 8 x 65,536
+// keys: 16 queries 746 us (64-key passes of 128 elements 765 us), 32 queries
+// 804 us (64 keys, 4 buffers: 815 us), 64 queries 905 us (64 keys, 4 buffers: 955 us);
+// 128 queries on 4 x 65,536 keys of d = 2048: 306 us (256 keys, 3 buffers: 299 us, but
+// 81 against 48 us on one set of 7,000 keys).
+template <knn_dtype DT, int MQ, int WK, int WQ, int NB, bool NORMS, int PK, int SPAN, int FM = 0>
+hipError_t launch_one(const DistArgs &a, int64_t n_tiles, int64_t groups, dim3 grid, hipStream_t st) {
+    hipLaunchKernelGGL((k_dist_mfma<DT, MQ, WK, WQ, NB, NORMS, PK, SPAN, FM>), grid, dim3(WK * WQ * kWave), 0, st, a,
+                       n_tiles, groups);
+    return hipGetLastError();
+}
+
 template <knn_dtype DT, bool NORMS>
 hipError_t launch_mq(int mq, const DistArgs &a, int64_t n_tiles, int64_t groups, dim3 grid, hipStream_t st,
                      int fm) {
-    const dim3 b4(4 * kWave), b8(8 * kWave);
     if (fm != 0) {  // the fused select: 128-query workgroups only
         if (mq != 8) return hipErrorInvalidValue;
-        if (fm == 1)
-            hipLaunchKernelGGL((k_dist_mfma<DT, 8, 4, 2, 2, NORMS, 256, 64, 1>), grid, b8, 0, st, a, n_tiles, groups);
-        else
-            hipLaunchKernelGGL((k_dist_mfma<DT, 8, 4, 2, 2, NORMS, 256, 64, 2>), grid, b8, 0, st, a, n_tiles, groups);
-        return hipGetLastError();
+        if (fm == 1) return launch_one<DT, 8, 2, 4, 4, NORMS, 128, 64, 1>(a, n_tiles, groups, grid, st);
+        return launch_one<DT, 8, 2, 4, 4, NORMS, 128, 64, 2>(a, n_tiles, groups, grid, st);
     }
+    const int tile = a.rows_per_tile;
     switch (mq) {
-    case 1: hipLaunchKernelGGL((k_dist_mfma<DT, 1, 4, 1, 4, NORMS, 128, 128>), grid, b4, 0, st, a, n_tiles, groups); break;
-    case 2: hipLaunchKernelGGL((k_dist_mfma<DT, 2, 4, 1, 3, NORMS, 128, 128>), grid, b4, 0, st, a, n_tiles, groups); break;
-    case 4: hipLaunchKernelGGL((k_dist_mfma<DT, 4, 4, 1, 3, NORMS, 128, 128>), grid, b4, 0, st, a, n_tiles, groups); break;
-    case 8: hipLaunchKernelGGL((k_dist_mfma<DT, 8, 4, 2, 2, NORMS, 256, 64>), grid, b8, 0, st, a, n_tiles, groups); break;
+    case 1:
+        if (tile == 32) return launch_one<DT, 1, 2, 1, 4, NORMS, 32, 128>(a, n_tiles, groups, grid, st);
+        if (tile == 64) return launch_one<DT, 1, 4, 1, 3, NORMS, 64, 128>(a, n_tiles, groups, grid, st);
+        return launch_one<DT, 1, 4, 1, 4, NORMS, 128, 64>(a, n_tiles, groups, grid, st);
+    case 2:
+        if (tile == 32) return launch_one<DT, 2, 2, 2, 4, NORMS, 32, 128>(a, n_tiles, groups, grid, st);
+        if (tile == 64) return launch_one<DT, 2, 4, 1, 3, NORMS, 64, 128>(a, n_tiles, groups, grid, st);
+        return launch_one<DT, 2, 4, 1, 3, NORMS, 128, 64>(a, n_tiles, groups, grid, st);
+    case 4:
+        if (tile == 32) return launch_one<DT, 4, 2, 2, 4, NORMS, 32, 128>(a, n_tiles, groups, grid, st);
+        if (tile == 64) return launch_one<DT, 4, 2, 2, 3, NORMS, 64, 128>(a, n_tiles, groups, grid, st);
+        return launch_one<DT, 4, 2, 2, 3, NORMS, 128, 64>(a, n_tiles, groups, grid, st);
+    case 8:
+        if (tile == 32) return launch_one<DT, 8, 2, 4, 3, NORMS, 32, 128>(a, n_tiles, groups, grid, st);
+        if (tile == 64) return launch_one<DT, 8, 2, 4, 4, NORMS, 64, 64>(a, n_tiles, groups, grid, st);
+        return launch_one<DT, 8, 2, 4, 4, NORMS, 128, 64>(a, n_tiles, groups, grid, st);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <knn_dtype DT>
@@ -392,19 +422,44 @@ hipError_t launch_dt(int mq, const DistArgs &a, int64_t n_tiles, int64_t groups,
 
 // Key rows per workgroup: at least 256, and enough that a tile runs at least
 // 64 pipeline steps of 128 keys x 128 elements, at most 4096 rows; always a
-// multiple of 256, so that both pass sizes divide it.
+// multiple of 256.
 int mfma_tile_rows(int64_t d) {
     const int64_t nspan = d / kSpan > 0 ? d / kSpan : 1;
     int64_t rows = (64 + nspan - 1) / nspan * 128;
-    rows = (rows + kTileQuantum - 1) / kTileQuantum * kTileQuantum;
-    if (rows < kTileQuantum) rows = kTileQuantum;
+    rows = (rows + 255) / 256 * 256;
     if (rows > 4096) rows = 4096;
     return static_cast<int>(rows);
 }
 
+// Finer tiles where those of `rows` would leave CUs idle.  Two or three
+// workgroups share a CU, so tiles are halved (down to one 128-key pass; 256
+// rows for 128-query groups on the long rows that the fused select may take)
+// while they are fewer than four for each CU; and where 64-row or 32-row tiles
+// still fit one a CU (two a CU for up to 32 queries at 64 rows: there the queries' share of
+// the loads is small), each workgroup's few keys are all in flight at once.
+// Measured at d = 4096, 128 / 64 / 32 rows a tile: 7,000 keys, 30 queries 33 / 22
+// / 17 us (256 rows 72 us); 2 x 7,000 keys, 16 queries 30 / 25 / 28 us; 4 x 7,000
+// keys, 32 queries 53 / 49 / 61 us, 64 queries 56 / 63 / 84 us; 8 sets of 4,000 to
+// 8,000 keys, 16 to 35 queries 82 / 114 / 137 us (256 rows 102 us).
+int mfma_fine_rows(int rows, int64_t S, int64_t max_keys, int64_t max_queries) {
+    constexpr int64_t kCus = 256;
+    const int64_t groups = (max_queries + 127) / 128;
+    auto blocks = [&](int64_t n) { return S * ((max_keys + n - 1) / n) * groups; };
+    if (S >= 4 * kCus) return rows;
+    const int64_t least = max_queries > 64 && max_keys > 65536 ? 256 : 128;
+    int64_t n = rows;
+    while (n > least && blocks(n) < 4 * kCus) n = (n / 2 + least - 1) / least * least;
+    if (n > 128) return static_cast<int>(n);
+    if (blocks(32) <= kCus) return 32;
+    if (blocks(64) <= (max_queries <= 32 ? 2 * kCus : kCus)) return 64;
+    return 128;
+}
+
 hipError_t launch_distances_mfma(int mq, knn_dtype dtype, const DistArgs &args, int64_t S, int64_t groups,
                                  hipStream_t stream, int fm) {
-    if (groups < 1 || args.rows_per_tile % kTileQuantum != 0 || args.d % kSpan != 0) return hipErrorInvalidConfiguration;
+    if (groups < 1 || args.d % kSpan != 0 ||
+        (args.rows_per_tile % kTileQuantum != 0 && args.rows_per_tile != 64 && args.rows_per_tile != 32))
+        return hipErrorInvalidConfiguration;
     if (fm != 0 && (args.sample_every < 1 || args.sample_rows < kTileQuantum || args.sample_rows % kTileQuantum != 0 ||
                     args.sample_rows > args.rows_per_tile))
         return hipErrorInvalidConfiguration;
