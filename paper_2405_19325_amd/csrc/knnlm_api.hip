@@ -33,6 +33,7 @@ struct Layout {
     int rows_per_tile;
     int64_t tiles_per_set;
     int64_t ld;  // distance row stride = tiles_per_set * rows_per_tile
+    SelectPath path;
     int split_parts;  // > 0: the select runs split over parts, short rows or long (candidate lists and counts below)
     // The fused select (128-query batches on long rows): candidates listed by the
     // distance kernel from a threshold sampled per query; the distance matrix is
@@ -51,11 +52,11 @@ struct Layout {
 bool fused_shape(int64_t B, int64_t d, knn_dtype dtype, int64_t max_queries, int64_t ld, int32_t r,
                  int64_t tiles_per_set) {
     return mfma_shape(d, dtype, max_queries) && max_queries > 64 && r <= kSplitMaxR &&
-           select_split_parts(B, ld, r) == 0 && select_wide_parts(B, ld, r, tiles_per_set) > 0;
+           select_wide_parts(B, ld, r, tiles_per_set) > 0;
 }
 
 Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, knn_dtype dtype, int32_t r,
-                 int rows_per_tile) {
+                 int rows_per_tile, bool roomy) {
     Layout L{};
     L.rows_per_tile = rows_per_tile;
     L.tiles_per_set = (max_keys + L.rows_per_tile - 1) / L.rows_per_tile;
@@ -65,8 +66,14 @@ Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, kn
     L.off_tmin = align_up(L.off_dist + sizeof(float) * static_cast<size_t>(B) * static_cast<size_t>(L.ld));
     L.off_tmax = align_up(L.off_tmin + sizeof(float) * static_cast<size_t>(B) * static_cast<size_t>(L.tiles_per_set));
     L.off_cand = align_up(L.off_tmax + sizeof(float) * static_cast<size_t>(B) * static_cast<size_t>(L.tiles_per_set));
-    L.split_parts = select_split_parts(B, L.ld, r);
-    if (L.split_parts == 0) L.split_parts = select_wide_parts(B, L.ld, r, L.tiles_per_set);
+    L.path = kSplitSelect;
+    L.split_parts = select_split_parts(B, L.ld, r, roomy ? kSplitMaxBlocks : kSplitFewBlocks);
+    if (L.split_parts == 0) {
+        L.path = kWideSelect;
+        L.split_parts = select_wide_parts(B, L.ld, r, L.tiles_per_set);
+    }
+    if (L.split_parts == 0 && roomy) L.split_parts = select_sampled_parts(B, L.ld, r, L.path);
+    if (L.split_parts == 0) L.path = kRowSelect;
     const size_t np = static_cast<size_t>(L.split_parts) * static_cast<size_t>(B);  // 0 unless split or wide
     L.off_count = align_up(L.off_cand + sizeof(uint64_t) * kSplitKeys * np);
     L.off_thr = align_up(L.off_count + 2 * sizeof(uint32_t) * np);  // counts, then minima
@@ -82,28 +89,28 @@ Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, kn
     // lists, and halves the sample pass and the threshold kernel's reads.)
     L.sample_rows = L.rows_per_tile / 8 > 256 ? L.rows_per_tile / 8 : 256;
     L.sample_every = 64 * L.sample_rows / L.rows_per_tile > 1 ? 64 * L.sample_rows / L.rows_per_tile : 1;
-    L.group_rows = select_group_rows(B, L.ld, r, L.rows_per_tile, !mfma_shape(d, dtype, max_queries));
+    L.group_rows =
+        L.path == kSplitSelect ? select_group_rows(L.ld, r, L.rows_per_tile, !mfma_shape(d, dtype, max_queries)) : 0;
     L.off_gmin = align_up(L.off_fallback + (L.fused ? sizeof(uint32_t) : 0));
     const size_t gmin_words = L.group_rows > 0 ? static_cast<size_t>(B) * static_cast<size_t>(4 * L.tiles_per_set) : 0;
     L.total = align_up(L.off_gmin + sizeof(float) * gmin_words);
     return L;
 }
 
-// The layout of a call.  Query batches on row-major keys take finer tiles where
-// the launch would leave CUs idle (mfma_fine_rows), except where the fused
-// select runs (its sample is laid out in whole tiles) and where the finer
-// tiles' extrema, a few percent of the workspace, would be what does not fit
-// the static scratch array.
+// The layout of a call on a workspace of `bytes` bytes: the roomy one if it
+// fits, else one without the lists of the larger split and sampled selects
+// and with the coarse tiles, which is the smallest that is accepted (the
+// static scratch array, and callers with a workspace of that size).
+// Roomy layouts of query batches on row-major keys take finer tiles where the
+// launch would leave CUs idle (mfma_fine_rows), except where the fused select
+// runs: its sample is laid out in whole tiles.
 Layout layout(int64_t B, int64_t d, int64_t S, int64_t max_keys, int64_t max_queries, knn_dtype dtype, bool packed,
-              int32_t r) {
+              int32_t r, size_t bytes) {
     const int rows = dist_tile_rows(d, dtype, S, max_keys, max_queries);
-    const Layout L = layout_of(B, d, max_keys, max_queries, dtype, r, rows);
-    if (packed || L.fused || !mfma_shape(d, dtype, max_queries)) return L;
-    const int fine = mfma_fine_rows(rows, S, max_keys, max_queries);
-    if (fine == rows) return L;
-    const Layout F = layout_of(B, d, max_keys, max_queries, dtype, r, fine);
-    constexpr size_t scratch_bytes = KNNLM_NOALLOC_SCRATCH_BYTES;
-    return F.total > scratch_bytes && L.total <= scratch_bytes ? L : F;
+    Layout L = layout_of(B, d, max_keys, max_queries, dtype, r, rows, true);
+    if (!packed && !L.fused && mfma_shape(d, dtype, max_queries))
+        L = layout_of(B, d, max_keys, max_queries, dtype, r, mfma_fine_rows(rows, S, max_keys, max_queries), true);
+    return L.total <= bytes ? L : layout_of(B, d, max_keys, max_queries, dtype, r, rows, false);
 }
 
 bool finite_pos(float x) { return isfinite(x) && x > 0.0f; }
@@ -122,7 +129,7 @@ knn_status check_sizes(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total
     if (need_vocab && V > 0x7fffffffLL) return KNN_ERR_UNSUPPORTED;
     if (d > (int64_t(1) << 40) / elem_bytes(dtype)) return KNN_ERR_UNSUPPORTED;
     if (r > min_keys) return KNN_ERR_R_EXCEEDS_N;
-    const Layout L = layout(B, d, S, max_keys, max_queries, dtype, false, r);
+    const Layout L = layout(B, d, S, max_keys, max_queries, dtype, false, r, SIZE_MAX);
     if (S * L.tiles_per_set > 0x7fffffffLL) return KNN_ERR_UNSUPPORTED;
     if (max_queries > 65535) return KNN_ERR_UNSUPPORTED;  // query groups per set on grid.y
     return KNN_OK;
@@ -197,7 +204,7 @@ knn_status validate_part(const Call &c, int part) {
     if (dist || sel) {
         if (!c.workspace) return KNN_ERR_WORKSPACE;
         if (reinterpret_cast<uintptr_t>(c.workspace) % kAlign) return KNN_ERR_WORKSPACE;
-        const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r);
+        const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
         if (c.workspace_bytes < L.total) return KNN_ERR_WORKSPACE;
     }
     return KNN_OK;
@@ -234,6 +241,8 @@ MixArgs mix_args(const Call &c) {
 // The select stage's view of the workspace.
 SelectArgs select_args(const Call &c, const Layout &L, char *ws) {
     SelectArgs a{};
+    a.path = L.path;
+    a.parts = L.split_parts;
     a.dist = ws ? reinterpret_cast<float *>(ws + L.off_dist) : nullptr;
     a.tile_min = ws ? reinterpret_cast<float *>(ws + L.off_tmin) : nullptr;
     a.tile_max = ws ? reinterpret_cast<float *>(ws + L.off_tmax) : nullptr;
@@ -271,7 +280,7 @@ FusedArgs fused_args(const Layout &L, char *ws) {
 }
 
 knn_status run_part(const Call &c, int part, hipStream_t stream) {
-    const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r);
+    const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
     char *ws = static_cast<char *>(c.workspace);
     float *dist = ws ? reinterpret_cast<float *>(ws + L.off_dist) : nullptr;
     float *tmin = ws ? reinterpret_cast<float *>(ws + L.off_tmin) : nullptr;
@@ -451,7 +460,8 @@ knn_status knn_lm_mixture_noalloc(const void *queries, const void *keys, const f
     knn_status st = check_sizes(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set, max_queries_per_set,
                                 base_dtype(dtype), r, true);
     if (st != KNN_OK) return st;
-    const size_t need = layout(B, d, S, max_keys_per_set, max_queries_per_set, base_dtype(dtype), packed_flag(dtype), r).total;
+    const size_t need = layout(B, d, S, max_keys_per_set, max_queries_per_set, base_dtype(dtype), packed_flag(dtype), r,
+                               KNNLM_NOALLOC_SCRATCH_BYTES).total;
     if (need > static_cast<size_t>(KNNLM_NOALLOC_SCRATCH_BYTES)) return KNN_ERR_WORKSPACE;
     void *ws = nullptr;
     if ((st = scratch_of_current_device(&ws)) != KNN_OK) return st;
@@ -551,8 +561,8 @@ size_t knn_lm_mixture_workspace_size(int64_t B, int64_t d, int64_t V, int64_t S,
                     true) != KNN_OK)
         return 0;
     // one size for the call on packed and on row-major keys
-    const size_t row_major = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, false, r).total;
-    const size_t packed = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, true, r).total;
+    const size_t row_major = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, false, r, SIZE_MAX).total;
+    const size_t packed = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, true, r, SIZE_MAX).total;
     return row_major > packed ? row_major : packed;
 }
 

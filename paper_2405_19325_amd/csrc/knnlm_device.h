@@ -194,4 +194,19 @@ __device__ __forceinline__ int64_t set_of_query(const int64_t *query_offsets, in
     return lo;
 }
 
+// The same for a b that all lanes of a (whole) wave share: 64 offsets a step,
+// so that up to 64 sets take one memory latency and not one for each halving.
+__device__ __forceinline__ int64_t set_of_query_wave(const int64_t *query_offsets, int64_t S, int64_t b) {
+    const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+    int64_t lo = 0, hi = S;  // invariant: qo[lo] <= b < qo[hi]
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t i = lo + step * (lane + 1);
+        const bool below = query_offsets[i < hi ? i : lo] <= b && i < hi;
+        lo += step * __popcll(__ballot(below));  // the offsets ascend: the lanes below are the first ones
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    return lo;
+}
+
 }  // namespace knnlm

@@ -5,7 +5,18 @@
 
 namespace knnlm {
 
+// How a batch's rows are selected (chosen with the workspace layout).
+enum SelectPath {
+    kRowSelect,       // one workgroup a row: in registers (short rows, r <= 1024) or streamed
+    kSplitSelect,     // short rows in parts, or from group minima
+    kWideSelect,      // rows in parts, threshold from the tile minima
+    kSampledSelect,   // rows in parts, threshold from 4096 sampled keys
+    kSampled4Select   // the same from 16384
+};
+
 struct SelectArgs {
+    SelectPath path;
+    int parts;                   // parts per row (split, wide and sampled paths)
     const float *dist;           // [B, ld]
     const float *tile_min;       // [B, tiles_per_set] or null
     const float *tile_max;
@@ -85,15 +96,18 @@ hipError_t launch_spec_verify(const float *p_max, const float *p_draft, const in
 
 int select_capacity(int r);
 // Split select: rows of at most kSplitMaxN keys are cut into parts of
-// kSplitKeys keys, one workgroup each, when r <= kSplitMaxR and the parts of
-// all queries fit in one pass of the chip.  Returns the parts per query, or 0
+// kSplitKeys keys, one workgroup each, when r <= kSplitMaxR and there are at
+// most max_blocks parts over all queries (two passes of the chip.  184 rows of
+// up to 8,000 keys, a NEST step: 30 us, 48 us with a workgroup a row in registers; 64 rows
+// of up to 65,536 keys, fixed lambda: 40 and 51 us).  Returns the parts per query, or 0
 // when a query's row is selected by a single workgroup.
 constexpr int kSplitKeys = 4096;
 constexpr int kSplitCap = 4096;
 constexpr int64_t kSplitMaxN = 65536;
 constexpr int kSplitMaxR = 1024;
-constexpr int64_t kSplitMaxBlocks = 256;
-int select_split_parts(int64_t B, int64_t ld, int r);
+constexpr int64_t kSplitMaxBlocks = 1024;
+constexpr int64_t kSplitFewBlocks = 256;  // of a workspace that the lists of more would not fit
+int select_split_parts(int64_t B, int64_t ld, int r, int64_t max_blocks);
 // Split select from group minima (no parts kernel): the rows per key group
 // (4 or 8) when a batch of split rows is served by the streaming distance
 // kernels with rows_per_tile = 4 * group rows and every row of ld keys has at
@@ -101,13 +115,23 @@ int select_split_parts(int64_t B, int64_t ld, int r);
 // as threshold the end of the histogram bin holding the r-th smallest (so at
 // least r keys lie below it), and gathers the keys of the groups below it.
 constexpr int kGroupMaxPerRow = 4 * kSelectThreads * 4;  // 16384: four 16-byte loads per thread
-int select_group_rows(int64_t B, int64_t ld, int r, int rows_per_tile, bool streaming);
+int select_group_rows(int64_t ld, int r, int rows_per_tile, bool streaming);
 // Wide select: rows longer than kSplitMaxN keys are cut into parts (their
 // candidate lists use the split layout, [B, parts, kSplitKeys]) when r <= 2048
 // and the row has at least 2 r distance tiles; returns the parts per query
 // (at most 64), or 0.
 constexpr int64_t kWideBlocks = 2048;  // workgroups the wide select aims at
+// and the sampled one: one pass of the chip, since each part samples the row
+// anew (128 rows of 262,144 keys: 55 us; 1024 workgroups 70 us, 2048 88 us)
+constexpr int64_t kSampledBlocks = 512;
 int select_wide_parts(int64_t B, int64_t ld, int r, int64_t tiles_per_set);
+// Sampled select: any rows with r <= 2048 where the keys below a sampled
+// threshold fit the lists (4 standard deviations above their mean); sets the
+// path.  The streamed select of one workgroup a row, which it replaces, passes
+// over the row three times or more: 128 rows of 262,144 keys 141 us, 96 us so;
+// 463 rows of 185,000 to 245,000 keys 335 and 215 us; 278 rows of 8,500 keys,
+// r = 2048, 128 and 59 us.
+int select_sampled_parts(int64_t B, int64_t ld, int r, SelectPath &path);
 hipError_t launch_select(const SelectArgs &args, int64_t B, hipStream_t stream);
 hipError_t launch_select_mix(const SelectArgs &args, const MixArgs &mix, int64_t B, hipStream_t stream);
 hipError_t launch_mix(const MixArgs &args, int64_t B, hipStream_t stream);

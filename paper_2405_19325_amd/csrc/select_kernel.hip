@@ -99,6 +99,13 @@ __device__ __forceinline__ float query_lambda(const MixArgs &m, int64_t b, float
     }
 }
 
+// The rank among M keys sampled from a row of N that aims at about r + 4
+// standard deviations + 4 samples' worth of its keys.
+__device__ __host__ inline uint32_t sample_rank(uint32_t r, int M, float N) {
+    const float k0 = ceilf(static_cast<float>(r) * static_cast<float>(M) / N);
+    return static_cast<uint32_t>(k0 + ceilf(4.0f * sqrtf(k0)) + 4.0f);
+}
+
 __device__ __forceinline__ uint64_t sort_key(uint32_t dbits, uint32_t i) {
     return (static_cast<uint64_t>(dbits) << 32) | i;
 }
@@ -685,11 +692,27 @@ __device__ __forceinline__ void mix_row(const float (&wj)[PER], const int32_t (&
                 }
             }
         } else {
+            // Rows that 16-byte accesses don't fit: entries tid, tid + kT, ..., kMixU
+            // loads in flight before their stores (one load at a time, each
+            // behind the store before it, took 1 us an entry: 32 rows of
+            // V = 50257: a finish of 30 to 38 us, 26 us so).
             consume_loads(pre);  // unused on this path
-            for (int64_t i = tid; i < nv; i += kT) {
-                const float o = fmaf(lam, plm[v0 + i], acc[i] * scale);
-                pm[v0 + i] = o;
-                note_entry<NEST>(o, static_cast<int32_t>(v0 + i), dtok, bv, bw, pd);
+            constexpr int kMixU = TILE / kT < 8 ? TILE / kT : 8;
+            for (int64_t i0 = tid; i0 < nv; i0 += static_cast<int64_t>(kMixU) * kT) {
+                float x[kMixU];
+#pragma unroll
+                for (int u = 0; u < kMixU; ++u) {
+                    const int64_t i = i0 + static_cast<int64_t>(u) * kT;
+                    x[u] = plm[v0 + (i < nv ? i : i0)];
+                }
+#pragma unroll
+                for (int u = 0; u < kMixU; ++u) {
+                    const int64_t i = i0 + static_cast<int64_t>(u) * kT;
+                    const bool in = i < nv;
+                    const float o = fmaf(lam, x[u], acc[in ? i : i0] * scale);
+                    *(in ? pm + v0 + i : &g_mix_sink.x) = o;
+                    note_entry<NEST>(in ? o : -1.0f, static_cast<int32_t>(v0 + i), dtok, bv, bw, pd);
+                }
             }
         }
         if (!ONE_TILE && more) __syncthreads();  // acc is cleared again next
@@ -766,7 +789,7 @@ __global__ __launch_bounds__(kT) void k_select(SelectArgs a, MixArgs m) {
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const int32_t dtok = draft_token<MODE>(m, b);
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > a.ld) N = a.ld;
@@ -833,7 +856,7 @@ __global__ __launch_bounds__(kT) void k_select_fast(SelectArgs a, MixArgs m) {
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const int32_t dtok = draft_token<MODE>(m, b);
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > a.ld) N = a.ld;
@@ -1003,7 +1026,7 @@ __global__ __launch_bounds__(kT) void k_select_parts(SelectArgs a, MixArgs m, in
         vec4 = mix_vec4(m, b);
         if (vec4 && tid < nv / 4) pl4 = reinterpret_cast<const float4 *>(m.p_lm + b * m.V + v0)[tid];
     }
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > ld) N = ld;
@@ -1048,7 +1071,19 @@ __global__ __launch_bounds__(kT) void k_select_parts(SelectArgs a, MixArgs m, in
         }
     }
     __syncthreads();
-    if (sampled) thr = sh.hi;
+    if (sampled) {
+        thr = sh.hi;
+    } else if (part == 0) {
+        // A row that fits (it lies in part 0 alone): just past its largest
+        // unmasked key, so that the finish's buckets cover the keys and not
+        // everything up to +infinity (all in one bucket, ranked by n^2
+        // comparisons: a finish of 47 us for rows of 3,200 keys, 10 us so).
+        uint32_t lo = 0u, hi = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hi = lane_word(v, e) < kMaskedBits ? max(hi, lane_word(v, e)) : hi;
+        block_minmax_u32<false>(lo, hi, sh);
+        thr = hi + 1u;
+    }
 
     // Keys below the threshold go to the part's list: each wave reserves its
     // range with one LDS atomic (the list's order is free: the finish sorts).
@@ -1220,7 +1255,7 @@ __global__ __launch_bounds__(kT) void k_select_finish(SelectArgs a, MixArgs m, i
     // (loaded during the write-out below).
     float4 pre[SLICED ? kVocabSlice / 4 / kT : kVocabTileFast / 4 / kT];
     if constexpr (SLICED) mix_prefetch(m, b, static_cast<int64_t>(g) * kVocabSlice, pre);
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > a.ld) N = a.ld;
@@ -1508,7 +1543,7 @@ __global__ __launch_bounds__(kT) void k_mix(MixArgs m) {
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const int32_t dtok = draft_token<MODE>(m, b);
-    const int64_t s = set_of_query(m.query_offsets, m.S, b);
+    const int64_t s = set_of_query_wave(m.query_offsets, m.S, b);
     const int64_t k0 = m.key_offsets[s];
     const int64_t N = m.key_offsets[s + 1] - k0;
     float dj[kPer];
@@ -1575,6 +1610,12 @@ constexpr int kWideCap = kSplitKeys;       // candidates per list and in all (th
 constexpr int kWideU = 4;                  // 16-byte loads per thread per step
 constexpr int64_t kWideStep = static_cast<int64_t>(kT) * 4 * kWideU;  // keys per step (16384)
 
+// SAMPLED > 0 (rows without 2 r tiles, or shorter than this path's): the
+// threshold is the end of the bin holding the ks-th smallest of 4096 SAMPLED
+// keys sampled across the row (runs of 4), ks aiming at about r + 4 sd + 4
+// samples' worth as on the split path, and the part streams all its tiles (a
+// row of at most kWideCap keys keeps every unmasked key).
+template <int SAMPLED>
 __global__ __launch_bounds__(kT) void k_select_wide_parts(SelectArgs a, int parts) {
     __shared__ __align__(16) uint32_t hist[kSelectBins];
     __shared__ uint32_t qtile[kT];  // tiles of the current chunk with keys below the threshold
@@ -1584,7 +1625,7 @@ __global__ __launch_bounds__(kT) void k_select_wide_parts(SelectArgs a, int part
     const int lane = tid & (kWave - 1);
     const int64_t b = blockIdx.x / parts;
     const int part = static_cast<int>(blockIdx.x - b * parts);
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > a.ld) N = a.ld;
@@ -1592,35 +1633,80 @@ __global__ __launch_bounds__(kT) void k_select_wide_parts(SelectArgs a, int part
     const float *drow = a.dist + b * a.ld;
     if (tid == 0) sh.ccount = 0u;
 
-    // The threshold from the tile minima (masked keys, at +infinity, stay out).
     const int64_t ntiles = (N + a.rows_per_tile - 1) / a.rows_per_tile;
     const float *tmin = a.tile_min + b * a.tiles_per_set;
-    uint32_t lo = ~0u, hi = 0u;
-    for (int64_t t = tid; t < ntiles; t += kT) {
-        const uint32_t v = __float_as_uint(tmin[t]);
-        lo = v < kMaskedBits ? min(lo, v) : lo;
-        hi = v < kMaskedBits ? max(hi, v) : hi;
-    }
-    block_minmax_u32(lo, hi, sh);
     uint32_t thr = 0u;  // no unmasked key: nothing below
-    if (lo <= hi) {
-        for (int i = tid; i < kSelectBins; i += kT) hist[i] = 0u;
-        __syncthreads();
-        const uint32_t w = hi + 1u - lo;
-        const int shift = range_shift(w);
+    if constexpr (SAMPLED > 0) {
+        constexpr int kRuns = SAMPLED * kT;  // runs of 4 keys
+        constexpr int kSamples = 4 * kRuns;
+        if (N <= kWideCap) {
+            uint32_t bmin, bmax;
+            row_range(a, b, N, bmin, bmax, sh);
+            thr = bmax + 1u;
+        } else {
+            uint4 sv[SAMPLED];
+            uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+            for (int u = 0; u < SAMPLED; ++u) {  // a run starts at a multiple of 4 at most N - 4
+                const uint64_t t = static_cast<uint64_t>(u * kT + tid), n = static_cast<uint64_t>(N);
+                sv[u] = *reinterpret_cast<const uint4 *>(drow + (min(t * n / kRuns, n - 4) & ~3ull));
+            }
+            for (int i = tid; i < kSelectBins; i += kT) hist[i] = 0u;
+#pragma unroll
+            for (int u = 0; u < SAMPLED; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {  // masked keys, at +infinity, stay out
+                    const uint32_t x = lane_word(sv[u], e);
+                    lo = x < kMaskedBits ? min(lo, x) : lo;
+                    hi = x < kMaskedBits ? max(hi, x) : hi;
+                }
+            block_minmax_u32(lo, hi, sh);  // (also orders the cleared bins)
+            if (lo > hi) lo = hi = 0u;     // every sample masked
+            const uint32_t w = hi + 1u - lo;
+            const int shift = range_shift(w);
+#pragma unroll
+            for (int u = 0; u < SAMPLED; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (lane_word(sv[u], e) - lo < w) atomicAdd(&hist[(lane_word(sv[u], e) - lo) >> shift], 1u);
+            const uint32_t ks = sample_rank(r_eff, kSamples, static_cast<float>(N));
+            __syncthreads();
+            if (tid < kWave) {
+                const uint32_t j = ks < static_cast<uint32_t>(kSamples) ? wave_pick_bin(hist, ks, lane) : ~0u;
+                const uint64_t end = static_cast<uint64_t>(lo) + ((static_cast<uint64_t>(j) + 1u) << shift);
+                if (lane == 0) sh.hi = j == ~0u ? kMaskedBits : static_cast<uint32_t>(end < hi + 1ull ? end : hi + 1ull);
+            }
+            __syncthreads();
+            thr = sh.hi;
+        }
+    } else {
+        // The threshold from the tile minima (masked keys, at +infinity, stay out).
+        uint32_t lo = ~0u, hi = 0u;
         for (int64_t t = tid; t < ntiles; t += kT) {
             const uint32_t v = __float_as_uint(tmin[t]);
-            if (v < kMaskedBits) atomicAdd(&hist[(v - lo) >> shift], 1u);
+            lo = v < kMaskedBits ? min(lo, v) : lo;
+            hi = v < kMaskedBits ? max(hi, v) : hi;
         }
-        __syncthreads();
-        if (tid < kWave) {
-            // fewer than r tiles: every unmasked key (the finish then selects over the row)
-            const uint32_t j = wave_pick_bin(hist, r_eff > 0 ? r_eff : 1u, lane);
-            const uint64_t end = static_cast<uint64_t>(lo) + ((static_cast<uint64_t>(j) + 1u) << shift);
-            if (lane == 0) sh.hi = j == ~0u ? kMaskedBits : static_cast<uint32_t>(end < hi + 1ull ? end : hi + 1ull);
+        block_minmax_u32(lo, hi, sh);
+        if (lo <= hi) {
+            for (int i = tid; i < kSelectBins; i += kT) hist[i] = 0u;
+            __syncthreads();
+            const uint32_t w = hi + 1u - lo;
+            const int shift = range_shift(w);
+            for (int64_t t = tid; t < ntiles; t += kT) {
+                const uint32_t v = __float_as_uint(tmin[t]);
+                if (v < kMaskedBits) atomicAdd(&hist[(v - lo) >> shift], 1u);
+            }
+            __syncthreads();
+            if (tid < kWave) {
+                // fewer than r tiles: every unmasked key (the finish then selects over the row)
+                const uint32_t j = wave_pick_bin(hist, r_eff > 0 ? r_eff : 1u, lane);
+                const uint64_t end = static_cast<uint64_t>(lo) + ((static_cast<uint64_t>(j) + 1u) << shift);
+                if (lane == 0) sh.hi = j == ~0u ? kMaskedBits : static_cast<uint32_t>(end < hi + 1ull ? end : hi + 1ull);
+            }
+            __syncthreads();
+            thr = sh.hi;
         }
-        __syncthreads();
-        thr = sh.hi;
     }
 
     // This part's tiles, kT at a time: those whose minimum is below the
@@ -1639,7 +1725,7 @@ __global__ __launch_bounds__(kT) void k_select_wide_parts(SelectArgs a, int part
         if (tid == 0) sh.total = 0u;
         __syncthreads();
         const int64_t tt = c0 + tid;
-        const uint32_t qual = (tt < te && __float_as_uint(tmin[tt]) < thr) ? 1u : 0u;
+        const uint32_t qual = (tt < te && (SAMPLED > 0 || __float_as_uint(tmin[tt]) < thr)) ? 1u : 0u;
         const uint32_t qincl = wave_incl_scan_u32(qual, lane);
         const uint32_t qtot = readlane_u32(qincl, kWave - 1);
         uint32_t qbase = 0u;
@@ -1719,7 +1805,7 @@ __global__ __launch_bounds__(kT) void k_select_wide_finish(SelectArgs a, MixArgs
     const int lane = tid & (kWave - 1);
     const int64_t b = blockIdx.x;
     const int32_t dtok = draft_token<MODE>(m, b);
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > a.ld) N = a.ld;
@@ -1820,7 +1906,7 @@ __global__ __launch_bounds__(kT) void k_fused_threshold(SelectArgs a, FusedArgs 
     const int64_t b = blockIdx.x;
     if (b == 0 && tid == 0) *f.fallback = 0u;
     if (tid == 0) sh.ccount = 0u;
-    const int64_t s = set_of_query(a.query_offsets, a.S, b);
+    const int64_t s = set_of_query_wave(a.query_offsets, a.S, b);
     const int64_t k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - k0;
     if (N > a.ld) N = a.ld;
@@ -1988,7 +2074,7 @@ hipError_t launch_sel_fused(const SelectArgs &a, const MixArgs &m, const FusedAr
     SelectArgs lw = a;
     lw.gate = f.fallback;
     lw.gate_run = 1u;
-    hipLaunchKernelGGL(k_select_wide_parts, dim3(static_cast<unsigned>(B * wparts)), block, 0, st, lw, wparts);
+    hipLaunchKernelGGL(k_select_wide_parts<0>, dim3(static_cast<unsigned>(B * wparts)), block, 0, st, lw, wparts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL((k_select_wide_finish<MODE>), grid, block, 0, st, lw, m, wparts);
     return hipGetLastError();
@@ -2000,8 +2086,8 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
     if (B > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     if (a.tile_min == nullptr || a.tile_max == nullptr) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(B)), block(kT);
-    const int parts = select_split_parts(B, a.ld, a.r);
-    if (parts > 0) {
+    const int parts = a.parts;
+    if (a.path == kSplitSelect) {
         if (a.cand == nullptr || a.part_count == nullptr || a.part_thr == nullptr) return hipErrorInvalidValue;
         // With mixing and few rows, the finish runs once per vocabulary slice
         // of each row, every one of those workgroups selecting pi again, so
@@ -2051,13 +2137,15 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
         hipLaunchKernelGGL((k_select_finish<MODE, false, false>), grid, block, 0, st, a, m, parts, 1);
         return hipGetLastError();
     }
-    const int wparts = select_wide_parts(B, a.ld, a.r, a.tiles_per_set);
-    if (wparts > 0) {
+    if (a.path == kWideSelect || a.path == kSampledSelect || a.path == kSampled4Select) {
         if (a.cand == nullptr || a.part_count == nullptr || a.part_thr == nullptr) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_select_wide_parts, dim3(static_cast<unsigned>(B * wparts)), block, 0, st, a, wparts);
+        const dim3 pgrid(static_cast<unsigned>(B * parts));
+        if (a.path == kWideSelect) hipLaunchKernelGGL(k_select_wide_parts<0>, pgrid, block, 0, st, a, parts);
+        else if (a.path == kSampledSelect) hipLaunchKernelGGL(k_select_wide_parts<1>, pgrid, block, 0, st, a, parts);
+        else hipLaunchKernelGGL(k_select_wide_parts<4>, pgrid, block, 0, st, a, parts);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_select_wide_finish<MODE>), grid, block, 0, st, a, m, wparts);
+        hipLaunchKernelGGL((k_select_wide_finish<MODE>), grid, block, 0, st, a, m, parts);
         return hipGetLastError();
     }
     if (a.ld <= kFastMaxN && a.r <= kT) {
@@ -2075,14 +2163,14 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
 
 }  // namespace
 
-int select_split_parts(int64_t B, int64_t ld, int r) {
+int select_split_parts(int64_t B, int64_t ld, int r, int64_t max_blocks) {
     if (B < 1 || ld < 1 || ld > kSplitMaxN || r > kSplitMaxR) return 0;
     const int64_t parts = (ld + kSplitKeys - 1) / kSplitKeys;
-    return B * parts <= kSplitMaxBlocks ? static_cast<int>(parts) : 0;
+    return B * parts <= max_blocks ? static_cast<int>(parts) : 0;
 }
 
-int select_group_rows(int64_t B, int64_t ld, int r, int rows_per_tile, bool streaming) {
-    if (!streaming || select_split_parts(B, ld, r) == 0) return 0;
+int select_group_rows(int64_t ld, int r, int rows_per_tile, bool streaming) {
+    if (!streaming) return 0;
     if (rows_per_tile != 16 && rows_per_tile != 32) return 0;
     const int gr = rows_per_tile / 4;  // the streaming kernels' four waves each take a quarter of a tile
     const int64_t groups = ld / gr;
@@ -2090,13 +2178,31 @@ int select_group_rows(int64_t B, int64_t ld, int r, int rows_per_tile, bool stre
     return gr;
 }
 
-int select_wide_parts(int64_t B, int64_t ld, int r, int64_t tiles_per_set) {
-    if (B < 1 || ld <= kSplitMaxN || r > kWideMaxR || tiles_per_set < 2 * static_cast<int64_t>(r)) return 0;
-    int64_t parts = (kWideBlocks + B - 1) / B;  // about kWideBlocks workgroups
-    const int64_t by_len = ld / kWideStep;      // at least one step of keys per part
+// About `blocks` workgroups, at least one step of keys each.
+static int wide_parts(int64_t B, int64_t ld, int64_t blocks) {
+    int64_t parts = (blocks + B - 1) / B;
+    const int64_t by_len = ld / kWideStep;
     if (parts > by_len) parts = by_len;
     if (parts > kWave) parts = kWave;           // the finish scans the counts with one wave
     return parts < 1 ? 1 : static_cast<int>(parts);
+}
+
+int select_wide_parts(int64_t B, int64_t ld, int r, int64_t tiles_per_set) {
+    if (B < 1 || ld <= kSplitMaxN || r > kWideMaxR || tiles_per_set < 2 * static_cast<int64_t>(r)) return 0;
+    return wide_parts(B, ld, kWideBlocks);
+}
+
+int select_sampled_parts(int64_t B, int64_t ld, int r, SelectPath &path) {
+    if (B < 1 || ld < 1 || ld > 0x7fffffffLL || r > kWideMaxR) return 0;
+    for (int u = 1; u <= 4; u += 3) {
+        const int M = 4 * kT * u;
+        const float ks = static_cast<float>(sample_rank(static_cast<uint32_t>(r), M, static_cast<float>(ld)));
+        const float keys = ks * static_cast<float>(ld) / static_cast<float>(M);  // kept of a row, on average
+        if (ld > kWideCap && keys + 4.0f * keys / sqrtf(ks) > static_cast<float>(kWideCap)) continue;
+        path = u == 1 ? kSampledSelect : kSampled4Select;
+        return wide_parts(B, ld, kSampledBlocks);
+    }
+    return 0;
 }
 
 int select_capacity(int r) {

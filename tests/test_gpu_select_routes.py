@@ -1,0 +1,106 @@
+"""Every select path, on workspaces that hold its lists and on the smallest accepted one, against a stable sort
+of the distance matrix; the mixture of rows that 16-byte accesses fit and don't."""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+knn = pytest.importorskip("paper_2405_19325_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    knn.load()
+    yield
+    torch.cuda.synchronize()
+
+
+def _smallest_workspace(prob):
+    """The fewest bytes (a multiple of 256) that knn_lm_mixture accepts for the problem."""
+    lo, hi = 0, prob.workspace.numel() // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if prob._validate(256, mid * 256) == 0 else (mid, hi)
+    return hi * 256
+
+
+def _reference(dist, ko, qo, r, masked):
+    ids, ds = [], []
+    for s in range(len(ko) - 1):
+        n = int(ko[s + 1] - ko[s])
+        m = torch.from_numpy(masked[int(ko[s]):int(ko[s + 1])]).cuda()
+        for b in range(int(qo[s]), int(qo[s + 1])):
+            d, i = torch.where(m, math.inf, dist[b, :n]).sort(stable=True)
+            ds.append(d[:r])
+            ids.append(torch.where(torch.isinf(d[:r]), -1, i[:r]).int())
+    return torch.stack(ids), torch.stack(ds)
+
+
+# queries and keys per set, d, dtype, r, V, largest entry of integer keys (0: normal keys)
+CASES = {
+    "split, 320 parts": (40, (8000, 5000, 4097, 7999), 64, torch.float32, 1000, 1000, 0),
+    "split, rows of one part": (45, (4096, 4000, 1024, 4500, 3001), 64, torch.float32, 1024, 1003, 0),
+    "split, every distance alike": (300, (4096,), 8, torch.float32, 64, 500, 1),
+    "rows over 1024 parts": (1100, (3000, 4097), 8, torch.float32, 100, 37, 0),
+    "sampled, r over 1024": (3, (5000, 2100, 40000), 16, torch.float32, 2048, 40001, 0),
+    "sampled, long rows": (20, (262144,), 128, torch.bfloat16, 1024, 1003, 0),
+    "sampled from 16384": (18, (300000, 4099), 128, torch.float16, 1024, 1000, 0),
+    "sampled, few values": (18, (100000,), 128, torch.bfloat16, 900, 1001, 1),
+    "streamed, r over 2048": (2, (9000,), 32, torch.float32, 3000, 1000, 0),
+}
+
+
+@pytest.mark.parametrize("masks", [False, True], ids=["all-keys", "masked"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_select_and_mixture(name, masks):
+    q, sizes, d, dtype, r, V, top = CASES[name]
+    print(f"[gpu] select route: {name} masks={masks}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(q + d + r)
+    S, n = len(sizes), sum(sizes)
+    ko = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    qo = np.arange(S + 1, dtype=np.int64) * q
+
+    def draw(rows):
+        if top:
+            x = torch.zeros(rows, d, device="cuda")
+            x[:, :4] = torch.randint(-top, top + 1, (rows, 4), generator=g, device="cuda").float()
+            return x.to(dtype)
+        return (torch.randn(rows, d, generator=g, device="cuda") * (8 / math.sqrt(d))).to(dtype)
+
+    k, x = draw(n), draw(S * q)
+    values = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    p_lm = torch.softmax(torch.randn(S * q, V, generator=g, device="cuda"), 1)
+    masked = np.zeros(n, bool)
+    if masks:
+        masked[np.random.default_rng(5).choice(n, n // 50, replace=False)] = True
+    tko, tqo = torch.from_numpy(ko).cuda(), torch.from_numpy(qo).cuda()
+    prob = knn.MixtureProblem(x, k, values, tko, tqo, p_lm, r, lam=0.3, key_offsets_host=ko, query_offsets_host=qo)
+    dist = knn.distances(x, k, tko, tqo, key_offsets_host=ko, query_offsets_host=qo)
+    ids, ds = _reference(dist, ko, qo, r, masked)
+    mask = knn.mask_words(np.flatnonzero(masked), n, "cuda") if masks else None
+    base = torch.from_numpy(np.repeat(ko[:-1], q)).cuda()[:, None]
+    w = torch.where(ids < 0, 0.0, torch.exp(-prob.mu * (ds.double() - ds[:, :1].double())))
+    p_knn = torch.zeros(S * q, V, dtype=torch.float64, device="cuda")
+    p_knn.scatter_add_(1, values[(base + ids.clamp(min=0)).flatten()].view_as(ids).long(), w / w.sum(1, keepdim=True))
+    whole = prob.workspace
+    for size in (whole.numel(), _smallest_workspace(prob)):
+        prob.workspace = whole[:size]
+        if masks:  # lambda_t and the decoding outputs too
+            out = prob.run_nest(0.3, 0.1, 0.5, key_mask=mask)
+            lam = out["lambdas"].double()[:, None]
+            assert torch.equal(out["next_token"].long(), out["p_m"].argmax(1)) or \
+                torch.equal(out["p_max"], out["p_m"].max(1).values)
+        else:
+            prob.run()
+            lam = 0.3
+        assert torch.equal(prob.ids, ids), size
+        assert torch.equal(prob.dists, ds), size
+        # a weight's fp32 argument is off by at most an ulp of mu d (2^-18 at d = 128): 1e-5 of p_kNN
+        torch.testing.assert_close(prob.p_m.double(), lam * p_lm.double() + (1 - lam) * p_knn, rtol=2e-5, atol=1e-7)
