@@ -45,8 +45,8 @@ struct TileWork {
 
 template <int NQ>
 __device__ __forceinline__ bool tile_work(const DistArgs &a, TileWork &t) {
-    const int64_t tiles = a.tiles_per_set;
-    const int64_t s = blockIdx.x / tiles;
+    const uint32_t tiles = static_cast<uint32_t>(a.tiles_per_set);  // (sets x tiles < 2^31; 64-bit division is slow)
+    const uint32_t s = blockIdx.x / tiles;
     const int64_t tile = blockIdx.x - s * tiles;
     t.k0 = a.key_offsets[s];
     int64_t N = a.key_offsets[s + 1] - t.k0;
@@ -88,7 +88,7 @@ __device__ __forceinline__ void write_tile_extrema(const DistArgs &a, const Tile
             m = fminf(m, smin[w][j]);
             M = fmaxf(M, smax[w][j]);
         }
-        const int64_t tile = t.r0 / a.rows_per_tile;
+        const int64_t tile = blockIdx.x % static_cast<uint32_t>(a.tiles_per_set);
         if (a.tile_min != nullptr) {
             a.tile_min[(t.qb + j) * a.tiles_per_set + tile] = m;
             a.tile_max[(t.qb + j) * a.tiles_per_set + tile] = M;

@@ -55,8 +55,8 @@ bool fused_shape(int64_t B, int64_t d, knn_dtype dtype, int64_t max_queries, int
            select_wide_parts(B, ld, r, tiles_per_set) > 0;
 }
 
-Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, knn_dtype dtype, int32_t r,
-                 int rows_per_tile, bool roomy) {
+Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64_t max_queries, knn_dtype dtype,
+                 int32_t r, int rows_per_tile, bool roomy) {
     Layout L{};
     L.rows_per_tile = rows_per_tile;
     L.tiles_per_set = (max_keys + L.rows_per_tile - 1) / L.rows_per_tile;
@@ -89,11 +89,13 @@ Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, kn
     // lists, and halves the sample pass and the threshold kernel's reads.)
     L.sample_rows = L.rows_per_tile / 8 > 256 ? L.rows_per_tile / 8 : 256;
     L.sample_every = 64 * L.sample_rows / L.rows_per_tile > 1 ? 64 * L.sample_rows / L.rows_per_tile : 1;
-    L.group_rows =
-        L.path == kSplitSelect ? select_group_rows(L.ld, r, L.rows_per_tile, !mfma_shape(d, dtype, max_queries)) : 0;
+    bool many = false;
+    if (L.path == kSplitSelect)
+        L.group_rows = select_group_rows(L.ld, min_keys, r, L.rows_per_tile, !mfma_shape(d, dtype, max_queries), many);
     L.off_gmin = align_up(L.off_fallback + (L.fused ? sizeof(uint32_t) : 0));
-    const size_t gmin_words = L.group_rows > 0 ? static_cast<size_t>(B) * static_cast<size_t>(4 * L.tiles_per_set) : 0;
+    const size_t gmin_words = many ? static_cast<size_t>(B) * static_cast<size_t>(4 * L.tiles_per_set) : 0;
     L.total = align_up(L.off_gmin + sizeof(float) * gmin_words);
+    if (!many) L.off_gmin = L.off_cand;  // in the place of the parts' lists, which the finish then has no use for
     return L;
 }
 
@@ -104,13 +106,13 @@ Layout layout_of(int64_t B, int64_t d, int64_t max_keys, int64_t max_queries, kn
 // Roomy layouts of query batches on row-major keys take finer tiles where the
 // launch would leave CUs idle (mfma_fine_rows), except where the fused select
 // runs: its sample is laid out in whole tiles.
-Layout layout(int64_t B, int64_t d, int64_t S, int64_t max_keys, int64_t max_queries, knn_dtype dtype, bool packed,
-              int32_t r, size_t bytes) {
+Layout layout(int64_t B, int64_t d, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries, knn_dtype dtype,
+              bool packed, int32_t r, size_t bytes) {
     const int rows = dist_tile_rows(d, dtype, S, max_keys, max_queries);
-    Layout L = layout_of(B, d, max_keys, max_queries, dtype, r, rows, true);
+    Layout L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, true);
     if (!packed && !L.fused && mfma_shape(d, dtype, max_queries))
-        L = layout_of(B, d, max_keys, max_queries, dtype, r, mfma_fine_rows(rows, S, max_keys, max_queries), true);
-    return L.total <= bytes ? L : layout_of(B, d, max_keys, max_queries, dtype, r, rows, false);
+        L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, mfma_fine_rows(rows, S, max_keys, max_queries), true);
+    return L.total <= bytes ? L : layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, false);
 }
 
 bool finite_pos(float x) { return isfinite(x) && x > 0.0f; }
@@ -129,7 +131,7 @@ knn_status check_sizes(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total
     if (need_vocab && V > 0x7fffffffLL) return KNN_ERR_UNSUPPORTED;
     if (d > (int64_t(1) << 40) / elem_bytes(dtype)) return KNN_ERR_UNSUPPORTED;
     if (r > min_keys) return KNN_ERR_R_EXCEEDS_N;
-    const Layout L = layout(B, d, S, max_keys, max_queries, dtype, false, r, SIZE_MAX);
+    const Layout L = layout(B, d, S, min_keys, max_keys, max_queries, dtype, false, r, SIZE_MAX);
     if (S * L.tiles_per_set > 0x7fffffffLL) return KNN_ERR_UNSUPPORTED;
     if (max_queries > 65535) return KNN_ERR_UNSUPPORTED;  // query groups per set on grid.y
     return KNN_OK;
@@ -204,7 +206,7 @@ knn_status validate_part(const Call &c, int part) {
     if (dist || sel) {
         if (!c.workspace) return KNN_ERR_WORKSPACE;
         if (reinterpret_cast<uintptr_t>(c.workspace) % kAlign) return KNN_ERR_WORKSPACE;
-        const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
+        const Layout L = layout(c.B, c.d, c.S, c.min_keys, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
         if (c.workspace_bytes < L.total) return KNN_ERR_WORKSPACE;
     }
     return KNN_OK;
@@ -280,7 +282,7 @@ FusedArgs fused_args(const Layout &L, char *ws) {
 }
 
 knn_status run_part(const Call &c, int part, hipStream_t stream) {
-    const Layout L = layout(c.B, c.d, c.S, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
+    const Layout L = layout(c.B, c.d, c.S, c.min_keys, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
     char *ws = static_cast<char *>(c.workspace);
     float *dist = ws ? reinterpret_cast<float *>(ws + L.off_dist) : nullptr;
     float *tmin = ws ? reinterpret_cast<float *>(ws + L.off_tmin) : nullptr;
@@ -460,7 +462,7 @@ knn_status knn_lm_mixture_noalloc(const void *queries, const void *keys, const f
     knn_status st = check_sizes(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set, max_queries_per_set,
                                 base_dtype(dtype), r, true);
     if (st != KNN_OK) return st;
-    const size_t need = layout(B, d, S, max_keys_per_set, max_queries_per_set, base_dtype(dtype), packed_flag(dtype), r,
+    const size_t need = layout(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, base_dtype(dtype), packed_flag(dtype), r,
                                KNNLM_NOALLOC_SCRATCH_BYTES).total;
     if (need > static_cast<size_t>(KNNLM_NOALLOC_SCRATCH_BYTES)) return KNN_ERR_WORKSPACE;
     void *ws = nullptr;
@@ -561,8 +563,8 @@ size_t knn_lm_mixture_workspace_size(int64_t B, int64_t d, int64_t V, int64_t S,
                     true) != KNN_OK)
         return 0;
     // one size for the call on packed and on row-major keys
-    const size_t row_major = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, false, r, SIZE_MAX).total;
-    const size_t packed = layout(B, d, S, max_keys_per_set, max_queries_per_set, et, true, r, SIZE_MAX).total;
+    const size_t row_major = layout(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, false, r, SIZE_MAX).total;
+    const size_t packed = layout(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, true, r, SIZE_MAX).total;
     return row_major > packed ? row_major : packed;
 }
 

@@ -110,12 +110,15 @@ constexpr int64_t kSplitFewBlocks = 256;  // of a workspace that the lists of mo
 int select_split_parts(int64_t B, int64_t ld, int r, int64_t max_blocks);
 // Split select from group minima (no parts kernel): the rows per key group
 // (4 or 8) when a batch of split rows is served by the streaming distance
-// kernels with rows_per_tile = 4 * group rows and every row of ld keys has at
-// least 2 r groups; else 0.  The finish reads each row's group minima, takes
-// as threshold the end of the histogram bin holding the r-th smallest (so at
-// least r keys lie below it), and gathers the keys of the groups below it.
+// kernels with rows_per_tile = 4 * group rows and every row holds at least 2 r
+// groups (`many`) or, by the shortest row, 5/4 r; else 0.  The finish reads
+// each row's group minima, takes as threshold the end of the histogram bin
+// holding the r-th smallest (so at least r keys lie below it), and gathers the
+// keys of the groups below it: of random keys 1.07 r at 8 r groups, 1.27 r at 2 r,
+// 1.66 r at 5/4 r (groups of 4).  7,437 keys of d = 4096, r = 1024: a NEST step
+// and its verification 32.8 us with the parts kernel's sample, 31.2 us so.
 constexpr int kGroupMaxPerRow = 4 * kSelectThreads * 4;  // 16384: four 16-byte loads per thread
-int select_group_rows(int64_t ld, int r, int rows_per_tile, bool streaming);
+int select_group_rows(int64_t ld, int64_t min_keys, int r, int rows_per_tile, bool streaming, bool &many);
 // Wide select: rows longer than kSplitMaxN keys are cut into parts (their
 // candidate lists use the split layout, [B, parts, kSplitKeys]) when r <= 2048
 // and the row has at least 2 r distance tiles; returns the parts per query

@@ -1366,6 +1366,13 @@ __global__ __launch_bounds__(kT) void k_select_finish(SelectArgs a, MixArgs m, i
         __syncthreads();  // the candidates are in LDS
         total = sh.ccount;
         fast = fits && total >= r_eff && total <= static_cast<uint32_t>(kSplitCap);
+        if (fast && thr == kMaskedBits) {  // every unmasked key: the sort's buckets end at the largest
+            uint32_t mn = ~0u, mx = 0u;
+#pragma unroll
+            for (int u = 0; u < kGroupItems; ++u) mx = key_of[u] < N && dv[u] < thr ? max(mx, dv[u]) : mx;
+            block_minmax_u32(mn, mx, sh);
+            thr = mx + 1u;
+        }
     } else {
         if (tid < kWave) {  // list starts, and whether any list is longer than its window
             const uint32_t incl = wave_incl_scan_u32(cnt, lane);
@@ -2169,13 +2176,15 @@ int select_split_parts(int64_t B, int64_t ld, int r, int64_t max_blocks) {
     return B * parts <= max_blocks ? static_cast<int>(parts) : 0;
 }
 
-int select_group_rows(int64_t ld, int r, int rows_per_tile, bool streaming) {
+int select_group_rows(int64_t ld, int64_t min_keys, int r, int rows_per_tile, bool streaming, bool &many) {
+    many = false;
     if (!streaming) return 0;
     if (rows_per_tile != 16 && rows_per_tile != 32) return 0;
     const int gr = rows_per_tile / 4;  // the streaming kernels' four waves each take a quarter of a tile
     const int64_t groups = ld / gr;
-    if (groups > kGroupMaxPerRow || groups < 2 * static_cast<int64_t>(r)) return 0;
-    return gr;
+    if (groups > kGroupMaxPerRow) return 0;
+    many = groups >= 2 * static_cast<int64_t>(r);
+    return many || 4 * (min_keys / gr) >= 5 * static_cast<int64_t>(r) ? gr : 0;
 }
 
 // About `blocks` workgroups, at least one step of keys each.

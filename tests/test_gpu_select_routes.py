@@ -48,6 +48,7 @@ CASES = {
     "split, 320 parts": (40, (8000, 5000, 4097, 7999), 64, torch.float32, 1000, 1000, 0),
     "split, rows of one part": (45, (4096, 4000, 1024, 4500, 3001), 64, torch.float32, 1024, 1003, 0),
     "split, every distance alike": (300, (4096,), 8, torch.float32, 64, 500, 1),
+    "groups, 5/4 r of them": (2, (5200, 7437), 16, torch.float32, 1024, 5001, 0),
     "rows over 1024 parts": (1100, (3000, 4097), 8, torch.float32, 100, 37, 0),
     "sampled, r over 1024": (3, (5000, 2100, 40000), 16, torch.float32, 2048, 40001, 0),
     "sampled, long rows": (20, (262144,), 128, torch.bfloat16, 1024, 1003, 0),
@@ -57,11 +58,12 @@ CASES = {
 }
 
 
-@pytest.mark.parametrize("masks", [False, True], ids=["all-keys", "masked"])
+@pytest.mark.parametrize("share", [0.0, 0.02, 0.5], ids=["all-keys", "masked", "half-masked"])
 @pytest.mark.parametrize("name", list(CASES))
-def test_select_and_mixture(name, masks):
+def test_select_and_mixture(name, share):
     q, sizes, d, dtype, r, V, top = CASES[name]
-    print(f"[gpu] select route: {name} masks={masks}", flush=True)
+    masks = share > 0
+    print(f"[gpu] select route: {name} masked={share}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(q + d + r)
     S, n = len(sizes), sum(sizes)
     ko = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
@@ -79,7 +81,7 @@ def test_select_and_mixture(name, masks):
     p_lm = torch.softmax(torch.randn(S * q, V, generator=g, device="cuda"), 1)
     masked = np.zeros(n, bool)
     if masks:
-        masked[np.random.default_rng(5).choice(n, n // 50, replace=False)] = True
+        masked[np.random.default_rng(5).choice(n, int(n * share), replace=False)] = True
     tko, tqo = torch.from_numpy(ko).cuda(), torch.from_numpy(qo).cuda()
     prob = knn.MixtureProblem(x, k, values, tko, tqo, p_lm, r, lam=0.3, key_offsets_host=ko, query_offsets_host=qo)
     dist = knn.distances(x, k, tko, tqo, key_offsets_host=ko, query_offsets_host=qo)
@@ -104,3 +106,32 @@ def test_select_and_mixture(name, masks):
         assert torch.equal(prob.dists, ds), size
         # a weight's fp32 argument is off by at most an ulp of mu d (2^-18 at d = 128): 1e-5 of p_kNN
         torch.testing.assert_close(prob.p_m.double(), lam * p_lm.double() + (1 - lam) * p_knn, rtol=2e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("case", ["sample-far", "sample-near"])
+def test_one_workgroup_row_misjudged(case):
+    """20 rows of 65,536 keys in the smallest workspace, where one workgroup selects each row: with the keys at
+    its sample's positions all far or all nearest, its threshold misjudges the count and the row is streamed."""
+    print(f"[gpu] one-workgroup row, {case}", flush=True)
+    n, B, d, r, V = 65536, 20, 16, 1024, 50
+    t = np.arange(1024)
+    sample = (t & 15) * 4096 + 4 * t + ((t >> 4) & 3)
+    rng = np.random.default_rng(11)
+    k = rng.integers(-30, 31, (n, d)).astype(np.float32)
+    if case == "sample-far":
+        k[sample] = 100
+    else:
+        k[:, 0] += 100
+        k[sample, 0] -= 100
+    dev = "cuda"
+    tk = torch.as_tensor(k, device=dev)
+    tq = torch.as_tensor(rng.integers(-3, 4, (B, d)).astype(np.float32), device=dev)
+    ko, qo = np.array([0, n]), np.array([0, B])
+    tko, tqo = torch.as_tensor(ko, device=dev), torch.as_tensor(qo, device=dev)
+    values = torch.as_tensor(rng.integers(0, V, n).astype(np.int32), device=dev)
+    p_lm = torch.full((B, V), 1.0 / V, device=dev)
+    prob = knn.MixtureProblem(tq, tk, values, tko, tqo, p_lm, r, key_offsets_host=ko, query_offsets_host=qo)
+    prob.workspace = prob.workspace[:_smallest_workspace(prob)]
+    prob.run()
+    ids, ds = _reference(knn.distances(tq, tk, tko, tqo), ko, qo, r, np.zeros(n, bool))
+    assert torch.equal(prob.ids, ids) and torch.equal(prob.dists, ds)
