@@ -510,6 +510,32 @@ __device__ __forceinline__ int32_t draft_token(const MixArgs &m, int64_t b) {
     return (MODE == kMixNest && m.draft != nullptr) ? load_scalar_i32(m.draft + b) : -1;
 }
 
+// How a tile of n entries of rows that start off a 16-byte boundary is written:
+// `head` single entries, n4 16-byte words, single entries again.  (All single
+// where p_lm and p_m lie differently.)  Thread i writes entry i of the head and of
+// the rest, words i, i + kT, ....
+struct ShiftedTile {
+    int head;
+    int64_t n4;
+};
+
+__device__ __forceinline__ ShiftedTile shifted_tile(const float *plm, const float *pm, int64_t n) {
+    const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(pm)) & 15u;
+    ShiftedTile t{0, 0};
+    if (at != (static_cast<uint32_t>(reinterpret_cast<uintptr_t>(plm)) & 15u) || (at & 3u) != 0u) return t;
+    const int64_t head = ((16u - at) & 15u) / 4u;
+    t.head = static_cast<int>(head < n ? head : n);
+    t.n4 = (n - t.head) / 4;
+    return t;
+}
+
+// The thread that writes entry i of the tile.
+__device__ __forceinline__ int shifted_owner(const ShiftedTile &t, int64_t i) {
+    if (i < t.head) return static_cast<int>(i);
+    const int64_t j = i - t.head;
+    return static_cast<int>(j < 4 * t.n4 ? (j / 4) % kT : (j - 4 * t.n4) % kT);
+}
+
 // This thread's float4s of the p_LM tile starting at v0 (16-byte path only):
 // unconditional loads, lanes past the row reading its last float4 (or, off the
 // 16-byte path, the sink), so that no branch sits around them; those lanes'
@@ -692,28 +718,47 @@ __device__ __forceinline__ void mix_row(const float (&wj)[PER], const int32_t (&
                 }
             }
         } else {
-            // Rows that 16-byte accesses don't fit: entries tid, tid + kT, ..., kMixU
-            // loads in flight before their stores (one load at a time, each
-            // behind the store before it, took 1 us an entry: 32 rows of
-            // V = 50257: a finish of 30 to 38 us, 26 us so).
+            // Rows that start off a 16-byte boundary (V no multiple of 4): the
+            // entries up to the boundary, 16 bytes at a time from there with
+            // all of a thread's loads in flight before its stores, the rest.
+            // (Four bytes and one load at a time, each behind the store before
+            // it, 32 rows of V = 50257 took a finish of 30 to 38 us, eight loads at a
+            // time 26 us, so 24 us.)
             consume_loads(pre);  // unused on this path
-            constexpr int kMixU = TILE / kT < 8 ? TILE / kT : 8;
-            for (int64_t i0 = tid; i0 < nv; i0 += static_cast<int64_t>(kMixU) * kT) {
-                float x[kMixU];
+            const ShiftedTile t = shifted_tile(plm + v0, pm + v0, nv);
+            auto entry = [&](int64_t i) __attribute__((always_inline)) {
+                const float o = fmaf(lam, plm[v0 + i], acc[i] * scale);
+                pm[v0 + i] = o;
+                note_entry<NEST>(o, static_cast<int32_t>(v0 + i), dtok, bv, bw, pd);
+            };
+            if (tid < t.head) entry(tid);
+            const float4 *src = reinterpret_cast<const float4 *>(plm + v0 + t.head);
+            float4 *dst = reinterpret_cast<float4 *>(pm + v0 + t.head);
+            if (t.n4 > 0) {
+                float4 x[kV4];
 #pragma unroll
-                for (int u = 0; u < kMixU; ++u) {
-                    const int64_t i = i0 + static_cast<int64_t>(u) * kT;
-                    x[u] = plm[v0 + (i < nv ? i : i0)];
-                }
+                for (int q = 0; q < kV4; ++q) x[q] = src[min(static_cast<int64_t>(q) * kT + tid, t.n4 - 1)];
 #pragma unroll
-                for (int u = 0; u < kMixU; ++u) {
-                    const int64_t i = i0 + static_cast<int64_t>(u) * kT;
-                    const bool in = i < nv;
-                    const float o = fmaf(lam, x[u], acc[in ? i : i0] * scale);
-                    *(in ? pm + v0 + i : &g_mix_sink.x) = o;
-                    note_entry<NEST>(in ? o : -1.0f, static_cast<int32_t>(v0 + i), dtok, bv, bw, pd);
+                for (int q = 0; q < kV4; ++q) {
+                    const int64_t i = static_cast<int64_t>(q) * kT + tid;
+                    const bool in = i < t.n4;
+                    const float *a4 = acc + t.head + 4 * (in ? i : 0);
+                    float4 o;
+                    o.x = fmaf(lam, x[q].x, a4[0] * scale);
+                    o.y = fmaf(lam, x[q].y, a4[1] * scale);
+                    o.z = fmaf(lam, x[q].z, a4[2] * scale);
+                    o.w = fmaf(lam, x[q].w, a4[3] * scale);
+                    *(in ? dst + i : &g_mix_sink) = o;
+                    if constexpr (NEST) {
+                        const int32_t w = static_cast<int32_t>(v0 + t.head + 4 * i);
+                        note_entry<NEST>(in ? o.x : -1.0f, w, dtok, bv, bw, pd);
+                        note_entry<NEST>(in ? o.y : -1.0f, w + 1, dtok, bv, bw, pd);
+                        note_entry<NEST>(in ? o.z : -1.0f, w + 2, dtok, bv, bw, pd);
+                        note_entry<NEST>(in ? o.w : -1.0f, w + 3, dtok, bv, bw, pd);
+                    }
                 }
             }
+            for (int64_t i = t.head + 4 * t.n4 + tid; i < nv; i += kT) entry(i);
         }
         if (!ONE_TILE && more) __syncthreads();  // acc is cleared again next
         v0 += TILE;
@@ -726,10 +771,15 @@ __device__ __forceinline__ void mix_row(const float (&wj)[PER], const int32_t (&
         uint32_t wtu = static_cast<uint32_t>(bw);
         block_argmax(top, wtu, red);
         if (m.p_draft != nullptr) {
-            // entry w was written by thread (w / 4) % kT on the 16-byte path, w % kT otherwise
+            // entry w was written by thread (w / 4) % kT on the 16-byte path, by its tile's owner of it otherwise
             const bool valid = dtok >= 0 && dtok < m.V;
-            const bool mine = valid && dtok >= c0 && dtok < end &&
-                              (vec4 ? ((dtok / 4) % kT == tid) : (dtok % kT == tid));
+            bool mine = valid && dtok >= c0 && dtok < end;
+            if (mine && vec4) {
+                mine = (dtok / 4) % kT == tid;
+            } else if (mine) {
+                const int64_t vt = c0 + (dtok - c0) / TILE * TILE, nv = end - vt < TILE ? end - vt : TILE;
+                mine = shifted_owner(shifted_tile(plm + vt, pm + vt, nv), dtok - vt) == tid;
+            }
             if (mine) m.p_draft[b] = pd;
             if (tid == 0 && first_slice && !valid) m.p_draft[b] = 0.0f;
         }
@@ -1157,6 +1207,28 @@ __device__ __forceinline__ void finish_sort(uint64_t *cand, uint32_t total, uint
                                              NoHook(), keep);
 }
 
+// Ascending sort of the n <= kRankMax keys in cand[0, n), in place: each key's
+// rank by comparison, eight threads a key (16 keys each, the same for a whole
+// wave), their counts added in LDS.  Two barriers where the bucket sort takes
+// five: 4 queries on 16,384 keys with r = 64, 19.0 us a step and 18.2 us so.
+// rank[0, kRankMax) is zero on entry, ordered by a barrier.
+constexpr int kRankMax = 128;
+__device__ __forceinline__ void rank_sort(uint64_t *cand, uint32_t n, uint32_t *rank) {
+    const uint32_t i = threadIdx.x & (kRankMax - 1);
+    const uint32_t j0 = threadIdx.x / kRankMax * (kRankMax * kRankMax / kT);
+    const uint64_t key = i < n ? cand[i] : ~0ull;
+    uint32_t below = 0u;
+#pragma unroll
+    for (uint32_t u = 0; u < kRankMax * kRankMax / kT; ++u) {
+        const uint64_t other = cand[j0 + u];  // (inside the buffer; entries past n are not counted)
+        below += (j0 + u < n && other < key) ? 1u : 0u;
+    }
+    if (i < n && below > 0u) atomicAdd(&rank[i], below);
+    __syncthreads();
+    if (threadIdx.x < n) cand[rank[i]] = key;
+    __syncthreads();
+}
+
 // Zeroes the sliced finish's fixed-point vocabulary tile (32 bytes per thread).
 __device__ __forceinline__ void clear_slice_tile(uint64_t *acc_s) {
     static_assert(kVocabSlice == 4 * kT, "four entries per thread");
@@ -1442,7 +1514,9 @@ __global__ __launch_bounds__(kT) void k_select_finish(SelectArgs a, MixArgs m, i
             }
             __syncthreads();  // the candidates are in LDS
         }
-        if (total <= static_cast<uint32_t>(kSplitCap / 2))
+        if (total <= static_cast<uint32_t>(kRankMax))
+            rank_sort(cand, total, hist);
+        else if (total <= static_cast<uint32_t>(kSplitCap / 2))
             finish_sort<PER / 2>(cand, total, lo, thr, hist, tmp, sh, r_eff);
         else
             finish_sort<PER>(cand, total, lo, thr, hist, tmp, sh, r_eff);

@@ -135,3 +135,35 @@ def test_one_workgroup_row_misjudged(case):
     prob.run()
     ids, ds = _reference(knn.distances(tq, tk, tko, tqo), ko, qo, r, np.zeros(n, bool))
     assert torch.equal(prob.ids, ids) and torch.equal(prob.dists, ds)
+
+
+@pytest.mark.parametrize("offset", [0, 1], ids=["rows alike", "rows off by four bytes"])
+@pytest.mark.parametrize("V", [5, 1003, 4099, 33001])
+@pytest.mark.parametrize("B,r", [(3, 64), (3, 300), (40, 64)])
+def test_rows_off_a_16_byte_boundary(B, r, V, offset):
+    """p_M and the decoding outputs of rows whose length is no multiple of four, by slices and whole, with p_LM
+    lying as p_M does or not; r = 64 sorts its candidates by rank."""
+    print(f"[gpu] odd rows B={B} r={r} V={V} offset={offset}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    n, d = 6000, 8
+    k, x = (torch.randn(m, d, generator=g, device="cuda") for m in (n, B))
+    values = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    flat = torch.empty(B * V + 1, device="cuda")
+    p_lm = flat[offset:offset + B * V].view(B, V)
+    p_lm.copy_(torch.softmax(torch.randn(B, V, generator=g, device="cuda"), 1))
+    drafts = torch.randint(0, V, (B,), generator=g, device="cuda", dtype=torch.int32)
+    drafts[:3] = torch.tensor([0, V - 1, min(V - 1, 4097)], device="cuda")
+    off, qo = torch.tensor([0, n], device="cuda"), torch.tensor([0, B], device="cuda")
+    prob = knn.MixtureProblem(x, k, values, off, qo, p_lm, r)
+    out = prob.run_nest(0.3, 0.1, 0.5, draft_tokens=drafts)
+    d64 = torch.cdist(x.double(), k.double()).square()
+    ds, ids = d64.topk(r, largest=False)
+    assert torch.equal(out["ids"].sort(1).values, ids.int().sort(1).values)
+    w = torch.exp(-prob.mu * (ds - ds[:, :1]))
+    p_knn = torch.zeros(B, V, dtype=torch.float64, device="cuda").scatter_add_(1, values[ids].long(), w / w.sum(1, True))
+    lam = out["lambdas"].double()[:, None]
+    torch.testing.assert_close(out["p_m"].double(), lam * p_lm.double() + (1 - lam) * p_knn, rtol=2e-5, atol=1e-7)
+    assert torch.equal(out["p_draft"], out["p_m"].gather(1, drafts.long()[:, None])[:, 0])
+    assert torch.equal(out["p_max"], out["p_m"].max(1).values)
+    first = (out["p_m"] == out["p_max"][:, None]).int().argmax(1)
+    assert torch.equal(out["next_token"].long(), first)
