@@ -115,6 +115,14 @@ Layout layout(int64_t B, int64_t d, int64_t S, int64_t min_keys, int64_t max_key
     return L.total <= bytes ? L : layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, false);
 }
 
+// The least workspace that a call is accepted with: the small layout on the
+// coarse tiles, also where a call's own tiles would need less.
+size_t least_workspace(int64_t B, int64_t d, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries,
+                       knn_dtype dtype, int32_t r) {
+    return layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, dist_tile_rows(d, dtype, S, max_keys, max_queries),
+                     false).total;
+}
+
 bool finite_pos(float x) { return isfinite(x) && x > 0.0f; }
 
 knn_status check_sizes(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total_keys,
@@ -206,8 +214,8 @@ knn_status validate_part(const Call &c, int part) {
     if (dist || sel) {
         if (!c.workspace) return KNN_ERR_WORKSPACE;
         if (reinterpret_cast<uintptr_t>(c.workspace) % kAlign) return KNN_ERR_WORKSPACE;
-        const Layout L = layout(c.B, c.d, c.S, c.min_keys, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
-        if (c.workspace_bytes < L.total) return KNN_ERR_WORKSPACE;
+        if (c.workspace_bytes < least_workspace(c.B, c.d, c.S, c.min_keys, c.max_keys, c.max_queries, c.dtype, c.r))
+            return KNN_ERR_WORKSPACE;
     }
     return KNN_OK;
 }
@@ -462,8 +470,7 @@ knn_status knn_lm_mixture_noalloc(const void *queries, const void *keys, const f
     knn_status st = check_sizes(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set, max_queries_per_set,
                                 base_dtype(dtype), r, true);
     if (st != KNN_OK) return st;
-    const size_t need = layout(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, base_dtype(dtype), packed_flag(dtype), r,
-                               KNNLM_NOALLOC_SCRATCH_BYTES).total;
+    const size_t need = least_workspace(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, base_dtype(dtype), r);
     if (need > static_cast<size_t>(KNNLM_NOALLOC_SCRATCH_BYTES)) return KNN_ERR_WORKSPACE;
     void *ws = nullptr;
     if ((st = scratch_of_current_device(&ws)) != KNN_OK) return st;

@@ -213,3 +213,12 @@ def test_select_path_rules_match_the_workspace_layout(lib):
     assert select_paths.tile_rows(256, 2, 32, 4096) == 64
     assert select_paths.split_path(32, 256, 2, 32, 4096, 1, 256, V=32000) == "parts"
     assert ws(**many) == ws(**dict(many, r=255))
+
+
+def test_least_workspace_is_that_of_whole_tiles(lib):
+    """A query batch on a small row-major store takes finer tiles than the 4096 rows that it needs the workspace of."""
+    sizes = dict(B=128, d=256, V=32000, S=62, total_keys=16404, min_keys=3, max_keys=549, max_queries=18, dtype=1, r=3)
+    rows_and_lists = 128 * (4 * 4096 + 8 * 4096)
+    assert _ws_size(lib, dict(BASE, **sizes)) > rows_and_lists
+    assert _validate(lib, ws_bytes=_ws_size(lib, dict(BASE, **sizes)), **sizes) == OK
+    assert _validate(lib, ws_bytes=rows_and_lists, **sizes) == WORKSPACE
