@@ -134,6 +134,9 @@ int select_wide_parts(int64_t B, int64_t ld, int r, int64_t tiles_per_set);
 // over the row three times or more: 128 rows of 262,144 keys 141 us, 96 us so;
 // 463 rows of 185,000 to 245,000 keys 335 and 215 us; 278 rows of 8,500 keys,
 // r = 2048, 128 and 59 us.
+// Its lists (32 KiB each) stay under 128 MiB, or under the distances: 100,000
+// rows of 1,000 keys would need 3 GiB of them beside 0.8 GiB of the rest.
+constexpr int64_t kSampledMaxLists = 4096;
 int select_sampled_parts(int64_t B, int64_t ld, int r, SelectPath &path);
 hipError_t launch_select(const SelectArgs &args, int64_t B, hipStream_t stream);
 hipError_t launch_select_mix(const SelectArgs &args, const MixArgs &mix, int64_t B, hipStream_t stream);

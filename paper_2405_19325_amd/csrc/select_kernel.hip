@@ -2282,8 +2282,10 @@ int select_sampled_parts(int64_t B, int64_t ld, int r, SelectPath &path) {
         const float ks = static_cast<float>(sample_rank(static_cast<uint32_t>(r), M, static_cast<float>(ld)));
         const float keys = ks * static_cast<float>(ld) / static_cast<float>(M);  // kept of a row, on average
         if (ld > kWideCap && keys + 4.0f * keys / sqrtf(ks) > static_cast<float>(kWideCap)) continue;
+        const int parts = wide_parts(B, ld, kSampledBlocks);
+        if (B * parts > kSampledMaxLists && parts * kSplitKeys * 8 > ld * 4) return 0;
         path = u == 1 ? kSampledSelect : kSampled4Select;
-        return wide_parts(B, ld, kSampledBlocks);
+        return parts;
     }
     return 0;
 }

@@ -222,3 +222,14 @@ def test_least_workspace_is_that_of_whole_tiles(lib):
     assert _ws_size(lib, dict(BASE, **sizes)) > rows_and_lists
     assert _validate(lib, ws_bytes=_ws_size(lib, dict(BASE, **sizes)), **sizes) == OK
     assert _validate(lib, ws_bytes=rows_and_lists, **sizes) == WORKSPACE
+
+
+@pytest.mark.parametrize("rows,keys,r", [(100_000, 1000, 64), (100_000, 4096, 1024), (10_000, 1000, 1000), (4096, 1000, 64)])
+def test_lists_of_many_short_rows_are_bounded(lib, rows, keys, r):
+    """A select's candidate lists take at most 128 MiB, or no more than the distances, the group minima and
+    extrema a tenth of those."""
+    S = rows // 10
+    size = _ws_size(lib, dict(BASE, B=rows, d=256, S=S, total_keys=keys * S, min_keys=keys, max_keys=keys,
+                              max_queries=10, r=r))
+    dist = 4 * rows * (keys + 256)  # the row rounded up to its tiles of at most 256
+    assert dist * keys // (keys + 256) < size < 1.2 * dist + max(dist, 129 << 20)
