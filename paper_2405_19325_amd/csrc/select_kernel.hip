@@ -1616,29 +1616,41 @@ __global__ __launch_bounds__(kT) void k_select_finish(SelectArgs a, MixArgs m, i
     }
 }
 
-// Standalone mixture on caller-given neighbours (any order): one workgroup per query.
-template <int MODE>
-__global__ __launch_bounds__(kT) void k_mix(MixArgs m) {
-    __shared__ __align__(16) float acc[kVocabTile];
+// Standalone mixture on caller-given neighbours (any order): one workgroup per
+// query, or (SLICED) one per slice of TILE entries of a query's row, each of
+// which takes the weights anew and adds those of its own tokens.  PER:
+// neighbours per thread.
+template <int MODE, int PER, int TILE, bool SLICED>
+__global__ __launch_bounds__(kT) void k_mix(MixArgs m, int slices) {
+    __shared__ __align__(16) float acc[TILE];
     __shared__ float red_f[kNumWaves];
     const int tid = threadIdx.x;
-    const int64_t b = blockIdx.x;
+    const int64_t b = SLICED ? blockIdx.x / static_cast<uint32_t>(slices) : blockIdx.x;
+    const int g = SLICED ? static_cast<int>(blockIdx.x - static_cast<uint32_t>(b) * static_cast<uint32_t>(slices)) : 0;
+    const int64_t c0 = static_cast<int64_t>(g) * TILE;
+    float4 pre[TILE / 4 / kT];
+    if constexpr (SLICED) mix_prefetch(m, b, c0, pre);
+    float dj[PER];
+    int32_t id[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int j = q * kT + tid;
+        dj[q] = j < m.r ? m.dists[b * m.r + j] : __builtin_huge_valf();
+        id[q] = j < m.r ? m.ids[b * m.r + j] : -1;
+    }
     const int32_t dtok = draft_token<MODE>(m, b);
     const int64_t s = set_of_query_wave(m.query_offsets, m.S, b);
     const int64_t k0 = m.key_offsets[s];
     const int64_t N = m.key_offsets[s + 1] - k0;
-    float dj[kPer];
-    int32_t id[kPer];
     // a neighbour whose id lies outside [0, N) is absent: no weight, no part in
     // the softmax's maximum or (RRC) in the ratio
-    bool present[kPer];
+    bool present[PER];
+    int32_t tok[PER];
     float dmin = __builtin_huge_valf(), neg_dmax = __builtin_huge_valf();
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int j = q * kT + tid;
-        dj[q] = j < m.r ? m.dists[b * m.r + j] : __builtin_huge_valf();
-        id[q] = j < m.r ? m.ids[b * m.r + j] : -1;
-        present[q] = j < m.r && id[q] >= 0 && id[q] < N;
+    for (int q = 0; q < PER; ++q) {
+        present[q] = id[q] >= 0 && id[q] < N;
+        if constexpr (PER == 1) tok[q] = *(present[q] ? m.values + k0 + id[q] : reinterpret_cast<const int32_t *>(&g_mix_sink));
         if (present[q]) {
             dmin = fminf(dmin, dj[q]);
             neg_dmax = fminf(neg_dmax, -dj[q]);
@@ -1648,22 +1660,26 @@ __global__ __launch_bounds__(kT) void k_mix(MixArgs m) {
     float dmax = 0.0f;
     if constexpr (rrc_mode(MODE)) dmax = -block_min(neg_dmax, red_f);
     const bool any = dmin != __builtin_huge_valf();
-    const float lam = query_lambda<MODE>(m, b, any ? dmin : 0.0f, any ? dmax : 0.0f);
-    float wj[kPer];
-    int32_t tok[kPer];
-    uint64_t nkey[kPer];
+    const float lam = query_lambda<MODE>(m, b, any ? dmin : 0.0f, any ? dmax : 0.0f, g == 0);
+    float wj[PER];
+    uint64_t nkey[PER];
     float zpart = 0.0f;
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         wj[q] = present[q] ? expf(-m.mu * (dj[q] - dmin)) : 0.0f;
         zpart += wj[q];
-        tok[q] = present[q] ? m.values[k0 + id[q]] : -1;
+        if constexpr (PER == 1) tok[q] = present[q] ? tok[q] : -1;
+        else tok[q] = present[q] ? m.values[k0 + id[q]] : -1;  // (several loads before the minimum: 5% slower)
         nkey[q] = present[q] ? (static_cast<uint64_t>(__float_as_uint(dj[q])) << 32) | static_cast<uint32_t>(id[q])
                              : ~0ull;
     }
     const float z = block_sum(zpart, red_f);
-    float4 pre[kVocabTile / 4 / kT];
-    mix_row<kPer, kVocabTile, MODE == kMixNest, false>(wj, tok, nkey, z, lam, m, b, acc, pre, dtok);
+    if constexpr (SLICED) {
+        const int64_t c1 = m.V - c0 < TILE ? m.V : c0 + TILE;
+        mix_row<PER, TILE, false, true, true>(wj, tok, nkey, z, lam, m, b, acc, pre, dtok, c0, c1, slices, g == 0);
+    } else {
+        mix_row<PER, TILE, MODE == kMixNest, false>(wj, tok, nkey, z, lam, m, b, acc, pre, dtok);
+    }
 }
 
 // Wide path: rows longer than the split path's (ld > kSplitMaxN), r <= kWideMaxR,
@@ -2346,14 +2362,43 @@ hipError_t launch_select_mix(const SelectArgs &args, const MixArgs &mix, int64_t
     return mix.rrc ? launch_sel<kMixRrc>(args, mix, B, stream) : launch_sel<kMixFixed>(args, mix, B, stream);
 }
 
+template <int MODE, int TILE, bool SLICED>
+static hipError_t launch_mix_tile(const MixArgs &args, int64_t B, int64_t slices, hipStream_t st) {
+    const dim3 grid(static_cast<unsigned>(B * slices)), block(kT);
+    const int n = static_cast<int>(slices);
+    if (args.r <= kT) hipLaunchKernelGGL((k_mix<MODE, 1, TILE, SLICED>), grid, block, 0, st, args, n);
+    else if (args.r <= 2 * kT) hipLaunchKernelGGL((k_mix<MODE, 2, TILE, SLICED>), grid, block, 0, st, args, n);
+    else hipLaunchKernelGGL((k_mix<MODE, kPer, TILE, SLICED>), grid, block, 0, st, args, n);
+    return hipGetLastError();
+}
+
+// The smallest slices that leave at most a workgroup per CU: past that the
+// weights, which every slice takes anew, cost more than the shorter rows save
+// (64 rows of V = 32000, r = 1024: 8 slices 9.1 us, 4 slices 7.2 us, whole rows 9.6
+// us).  Rows of one 32768-entry slice stay with the 8192-entry tiles, whose 32 KiB
+// let two workgroups share a CU (256 rows of V = 32000: 15.3 and 13.6 us).  A
+// workgroup a row before and slices now, r = 1024: 1 row of V = 32000 8.4 and 4.9 us, 128
+// rows 10.2 and 9.2 us; 16 rows of V = 50257 18.0 and 6.3 us, 128 rows 26.2 and 14.4 us.
+// Two slices don't make up for more than 2048 weights (128 rows of V = 32000, r = 4096: 16.3
+// us, a workgroup a row 15.9 us).
+template <int MODE>
+static hipError_t launch_mix_mode(const MixArgs &args, int64_t B, hipStream_t st) {
+    auto slices = [&](int64_t tile) { return (args.V + tile - 1) / tile; };
+    auto fits = [&](int64_t tile) { return B <= kSliceMaxBlocks / slices(tile); };
+    if (args.V <= kVocabSlice || fits(kVocabSlice))
+        return launch_mix_tile<MODE, kVocabSlice, true>(args, B, slices(kVocabSlice), st);
+    if (fits(kVocabTile)) return launch_mix_tile<MODE, kVocabTile, true>(args, B, slices(kVocabTile), st);
+    if (fits(2 * kVocabTile) && (args.r <= 2 * kT || slices(2 * kVocabTile) > 2))
+        return launch_mix_tile<MODE, 2 * kVocabTile, true>(args, B, slices(2 * kVocabTile), st);
+    if (fits(4 * kVocabTile) && args.V > 4 * kVocabTile)
+        return launch_mix_tile<MODE, 4 * kVocabTile, true>(args, B, slices(4 * kVocabTile), st);
+    return launch_mix_tile<MODE, kVocabTile, false>(args, B, 1, st);
+}
+
 hipError_t launch_mix(const MixArgs &args, int64_t B, hipStream_t stream) {
     if (B == 0) return hipSuccess;
     if (B > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    if (args.rrc)
-        hipLaunchKernelGGL(k_mix<kMixRrc>, dim3(static_cast<unsigned>(B)), dim3(kT), 0, stream, args);
-    else
-        hipLaunchKernelGGL(k_mix<kMixFixed>, dim3(static_cast<unsigned>(B)), dim3(kT), 0, stream, args);
-    return hipGetLastError();
+    return args.rrc ? launch_mix_mode<kMixRrc>(args, B, stream) : launch_mix_mode<kMixFixed>(args, B, stream);
 }
 
 }  // namespace knnlm
