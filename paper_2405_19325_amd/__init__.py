@@ -30,8 +30,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None):
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current stream's handle, without a Stream object around it (2.9 us of a call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
 
