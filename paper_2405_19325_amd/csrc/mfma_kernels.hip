@@ -35,6 +35,7 @@
 // end read on in its last pass's rows.
 #include "knnlm_internal.h"
 #include "mfma_device.h"
+#include "tile_rows.h"
 
 namespace knnlm {
 
@@ -106,13 +107,13 @@ __global__ __launch_bounds__(WK * WQ * kWave, 2) void k_dist_mfma(DistArgs a, in
     if (N > a.ld) N = a.ld;
     const int64_t qb = a.query_offsets[s] + grp * QB;
     const int64_t qe = a.query_offsets[s + 1];
-    // this workgroup's rows [r0, r1): the tile, its sample piece (FM 1), or the tile past its piece (FM 2)
-    int64_t r0 = tile * a.rows_per_tile;
-    const int64_t rend = r0 + (FM == 1 ? a.sample_rows : a.rows_per_tile);
-    if (FM == 2 && tile % se == 0) r0 += a.sample_rows;
-    if (qb >= qe || r0 >= N) return;  // uniform over the block
+    // this workgroup's rows [r0, r1): the tile, its sample piece (FM 1), or the
+    // tile past its piece (FM 2).  None past the set's end, and none where the
+    // piece is the whole tile: the loads below need a row to read.
+    const RowRange rows = mfma_rows(FM, tile, a.rows_per_tile, a.sample_rows, se, N);
+    const int64_t r0 = rows.first, r1 = rows.end;
+    if (qb >= qe || r0 >= r1) return;  // uniform over the block
     const int nq = static_cast<int>(qe - qb < QB ? qe - qb : QB);
-    const int64_t r1 = rend < N ? rend : N;
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(WK * WQ * kWave, 2) void k_dist_mfma(DistArgs a, in
         for (int i = 0; i < KLD; ++i) {
             const int k = min(wid * KLD + i, PK / kRowsPerLoad - 1);
             const int row = k * kRowsPerLoad + lrow;
-            koff[i] = min(p * PK + static_cast<uint32_t>(row), nrows - 1u) * rb + lcol(row);
+            koff[i] = mfma_load_row(p * PK + static_cast<uint32_t>(row), nrows) * rb + lcol(row);
         }
     };
     const char *kspan = kset + r0 * row_bytes, *qspan = qbase;  // the next step to load: its span of the rows

@@ -132,3 +132,35 @@ def test_fused_nest_step_with_masked_keys(layout):
     assert out["next_token"].cpu().numpy().tolist() == want["next_token"].tolist()
     assert out["span_key"].cpu().numpy().tolist() == want["span_key"].tolist()
     del tk, prob
+
+
+# One set, and two whose second ends at the allocation's end.  Rows of 65,537 to 81,920 keys take 257 to 320
+# tiles of 256 rows, every 64th of them wholly sampled: tile 256 is the last one (and short), or is followed by
+# a last tile of 8, 119 or 256 rows.
+@pytest.mark.parametrize("sizes", [(65536 + 100,), (65800,), (65792 + 119,), (66048,), (70001, 65800)],
+                         ids=lambda s: "-".join(map(str, s)))
+@pytest.mark.parametrize("d,queries", [(128, 66), (1024, 128)])
+def test_fused_select_of_wholly_sampled_tiles(d, queries, sizes):
+    """Tiles of 256 rows, as large as the sample's pieces: the listing pass has nothing to take of a sampled one."""
+    _say(f"fused select, 256-row tiles: d={d} {sizes}")
+    rng = np.random.default_rng(d + sum(sizes))
+    n, B, V = sum(sizes), queries * len(sizes), 500
+    k, q = np.zeros((n, d), np.float32), np.zeros((B, d), np.float32)
+    k[:, :8], q[:, :8] = rng.integers(-30, 31, (n, 8)), rng.integers(-30, 31, (B, 8))
+    vals = rng.integers(0, V, n).astype(np.int32)
+    p_lm = rng.dirichlet(np.ones(V), B).astype(np.float32)
+    ko = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    qo = np.arange(len(sizes) + 1, dtype=np.int64) * queries
+    dev = "cuda"
+    tk, tq = (torch.as_tensor(x, device=dev).to(torch.bfloat16) for x in (k, q))
+    prob = knn.MixtureProblem(tq, tk, torch.as_tensor(vals, device=dev), torch.as_tensor(ko, device=dev),
+                              torch.as_tensor(qo, device=dev), torch.as_tensor(p_lm, device=dev), R, 0.01, 0.3,
+                              key_offsets_host=ko, query_offsets_host=qo)
+    p_m, ids, dists = prob.run()
+    torch.cuda.synchronize()
+    # (the entries past the eighth are 0)
+    o_ids, o_d = oracle.select(np.ascontiguousarray(q[:, :8]), np.ascontiguousarray(k[:, :8]), "f32", ko, qo, R)
+    np.testing.assert_array_equal(ids.cpu().numpy(), o_ids)
+    np.testing.assert_array_equal(dists.cpu().numpy().astype(np.float64), o_d)
+    np.testing.assert_allclose(p_m.cpu().numpy(), oracle.mix(o_ids, o_d, vals, ko, qo, p_lm, 0.01, 0.3),
+                               rtol=0, atol=1e-5)

@@ -1,0 +1,69 @@
+"""The row ranges of the matrix-core distance workgroups (csrc/tile_rows.h), compiled for the host: every row a
+workgroup loads lies inside its set, and the passes of the fused select take every row once."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = """
+#include "tile_rows.h"
+extern "C" {
+void rows_of(int fm, int64_t tile, int64_t rpt, int64_t sr, int64_t se, int64_t n, int64_t *out) {
+    const knnlm::RowRange r = knnlm::mfma_rows(fm, tile, rpt, sr, se, n);
+    out[0] = r.first;
+    out[1] = r.end;
+}
+uint32_t load_row(uint32_t row, uint32_t nrows) { return knnlm::mfma_load_row(row, nrows); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tile_rows")
+    src, so = d / "shim.cpp", d / "shim.so"
+    src.write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2405_19325_amd", "csrc"), str(src), "-o", str(so)], check=True)
+    lib = ctypes.CDLL(str(so))
+    lib.rows_of.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 5 + [ctypes.c_void_p]
+    lib.load_row.argtypes = [ctypes.c_uint32] * 2
+    lib.load_row.restype = ctypes.c_uint32
+    return lib
+
+
+def _ranges(lib, fm, rpt, sr, se, n):
+    """(tile, first, end) of every workgroup of a pass that has rows."""
+    out = (ctypes.c_int64 * 2)()
+    tiles = (n + rpt - 1) // rpt
+    for t in range(0, tiles, se if fm == 1 else 1):
+        lib.rows_of(fm, t, rpt, sr, se, n, out)
+        if out[0] < out[1]:
+            yield t, out[0], out[1]
+
+
+# rows per tile, sample rows, sampled every: whole tiles sampled (256 of 256) and pieces of them
+@pytest.mark.parametrize("rpt,sr,se", [(256, 256, 64), (512, 256, 32), (1024, 256, 16), (4096, 512, 8)])
+def test_rows_loaded_lie_in_the_set(lib, rpt, sr, se):
+    period = rpt * se
+    for n in (1, sr - 1, sr, sr + 1, rpt, rpt + 1, rpt + 120, period - 1, period + 1, period + sr, period + sr + 1,
+              period + rpt + 8, 4 * period + rpt + 8, 65800, 70000):
+        for fm in (0, 1, 2):
+            for t, first, end in _ranges(lib, fm, rpt, sr, se, n):
+                assert 0 <= first and end <= n
+                rows = end - first
+                for row in (0, rows - 1, rows, rows + 127, 4 * rpt):  # passes past the end and padding steps
+                    assert first <= first + lib.load_row(row, rows) < end
+        whole = [(a, b) for _, a, b in _ranges(lib, 0, rpt, sr, se, n)]
+        parts = sorted((a, b) for fm in (1, 2) for _, a, b in _ranges(lib, fm, rpt, sr, se, n))
+        for spans in (whole, parts):  # every row once
+            assert spans[0][0] == 0 and spans[-1][1] == n
+            assert all(x[1] == y[0] for x, y in zip(spans, spans[1:]))
+
+
+def test_a_wholly_sampled_tile_leaves_no_rows(lib):
+    out = (ctypes.c_int64 * 2)()
+    lib.rows_of(2, 256, 256, 256, 64, 65800, out)
+    assert out[0] >= out[1]
