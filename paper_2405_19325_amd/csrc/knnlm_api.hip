@@ -8,6 +8,7 @@
 
 #include "knnlm.h"
 #include "select_internal.h"
+#include "tile_rows.h"
 
 // The workspace of knn_lm_mixture_noalloc: one array per GPU, held from the
 // library's load until the process ends.  Host code never uses its name as an
@@ -82,13 +83,9 @@ Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64
     L.off_ticket = align_up(L.off_best + sizeof(uint64_t) * per_row);
     L.off_fallback = align_up(L.off_ticket + sizeof(uint32_t) * per_row);
     L.fused = fused_shape(B, d, dtype, max_queries, L.ld, r, L.tiles_per_set);
-    // The sample: the first sample_rows rows (whole 256-key passes) of every
-    // sample_every-th tile, 1/64 of the keys, in pieces small enough that the
-    // sample launch fills the chip.  (1/64 keeps about 2,300 candidates per
-    // query for r = 1024 against about 1,900 at 1/32, both well inside the
-    // lists, and halves the sample pass and the threshold kernel's reads.)
-    L.sample_rows = L.rows_per_tile / 8 > 256 ? L.rows_per_tile / 8 : 256;
-    L.sample_every = 64 * L.sample_rows / L.rows_per_tile > 1 ? 64 * L.sample_rows / L.rows_per_tile : 1;
+    const FusedSample sample = fused_sample(L.rows_per_tile);
+    L.sample_rows = sample.rows;
+    L.sample_every = sample.every;
     bool many = false;
     if (L.path == kSplitSelect)
         L.group_rows = select_group_rows(L.ld, min_keys, r, L.rows_per_tile, !mfma_shape(d, dtype, max_queries), many);

@@ -164,3 +164,25 @@ def test_fused_select_of_wholly_sampled_tiles(d, queries, sizes):
     np.testing.assert_array_equal(dists.cpu().numpy().astype(np.float64), o_d)
     np.testing.assert_allclose(p_m.cpu().numpy(), oracle.mix(o_ids, o_d, vals, ko, qo, p_lm, 0.01, 0.3),
                                rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("layout", ["row-major", "packed"])
+def test_fused_select_of_tiles_off_a_power_of_two(layout):
+    """d = 384: tiles of 2816 rows, an eighth of which is no whole number of passes."""
+    _say(f"fused select, d = 384, {layout}")
+    n, B, d, r, V = 460001, 66, 384, 64, 300  # 164 tiles, at least 2 r
+    rng = np.random.default_rng(384)
+    k, q = np.zeros((n, d), np.float32), np.zeros((B, d), np.float32)
+    k[:, :8], q[:, :8] = rng.integers(-30, 31, (n, 8)), rng.integers(-30, 31, (B, 8))
+    dev = "cuda"
+    tk, tq = (torch.as_tensor(x, device=dev).to(torch.float16) for x in (k, q))
+    ko, qo = np.array([0, n]), np.array([0, B])
+    values = torch.as_tensor(rng.integers(0, V, n).astype(np.int32), device=dev)
+    p_lm = torch.full((B, V), 1 / V, device=dev)
+    prob = knn.MixtureProblem(tq, tk, values, torch.as_tensor(ko, device=dev), torch.as_tensor(qo, device=dev), p_lm,
+                              r, 0.01, key_offsets_host=ko, query_offsets_host=qo,
+                              packed_keys=knn.pack_keys(tk) if layout == "packed" else None)
+    _, ids, dists = prob.run()
+    o_ids, o_d = oracle.select(np.ascontiguousarray(q[:, :8]), np.ascontiguousarray(k[:, :8]), "f32", ko, qo, r)
+    np.testing.assert_array_equal(ids.cpu().numpy(), o_ids)
+    np.testing.assert_array_equal(dists.cpu().numpy().astype(np.float64), o_d)

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from paper_2405_19325_amd import _lib
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "tile_rows.h"
@@ -14,6 +16,11 @@ void rows_of(int fm, int64_t tile, int64_t rpt, int64_t sr, int64_t se, int64_t 
     const knnlm::RowRange r = knnlm::mfma_rows(fm, tile, rpt, sr, se, n);
     out[0] = r.first;
     out[1] = r.end;
+}
+void sample_of(int rpt, int *out) {
+    const knnlm::FusedSample s = knnlm::fused_sample(rpt);
+    out[0] = s.rows;
+    out[1] = s.every;
 }
 uint32_t load_row(uint32_t row, uint32_t nrows) { return knnlm::mfma_load_row(row, nrows); }
 }
@@ -67,3 +74,17 @@ def test_a_wholly_sampled_tile_leaves_no_rows(lib):
     out = (ctypes.c_int64 * 2)()
     lib.rows_of(2, 256, 256, 256, 64, 65800, out)
     assert out[0] >= out[1]
+
+
+def test_sample_of_every_width(lib):
+    """Every width's tiles have a sample that both matrix-core launchers take: whole passes (of at most 256 rows;
+    the packed kernel asks for whole blocks of 16), inside the tile, about 1/64 of the keys."""
+    tile_rows = _lib.load()["_ZN5knnlm14mfma_tile_rowsEl"]
+    tile_rows.argtypes, tile_rows.restype = [ctypes.c_int64], ctypes.c_int
+    out = (ctypes.c_int * 2)()
+    for d in range(128, 65536 + 1, 128):
+        rpt = tile_rows(d)
+        lib.sample_of(rpt, out)
+        rows, every = out
+        assert rows % 256 == 0 and 256 <= rows <= rpt and every >= 1, (d, rpt, rows, every)
+        assert 1 / 72 < rows / (rpt * every) < 1 / 48, (d, rpt, rows, every)
