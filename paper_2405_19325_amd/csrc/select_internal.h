@@ -95,6 +95,8 @@ hipError_t launch_spec_verify(const float *p_max, const float *p_draft, const in
                               int32_t *n_accept, int32_t *out_token, hipStream_t stream);
 
 int select_capacity(int r);
+// Whether the select of one workgroup a row holds the row in registers.
+bool select_in_registers(int64_t ld, int r);
 // Split select: rows of at most kSplitMaxN keys are cut into parts of
 // kSplitKeys keys, one workgroup each, when r <= kSplitMaxR and there are at
 // most max_blocks parts over all queries (two passes of the chip.  184 rows of

@@ -2245,7 +2245,7 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
         hipLaunchKernelGGL((k_select_wide_finish<MODE>), grid, block, 0, st, a, m, parts);
         return hipGetLastError();
     }
-    if (a.ld <= kFastMaxN && a.r <= kT) {
+    if (select_in_registers(a.ld, a.r)) {
         hipLaunchKernelGGL((k_select_fast<MODE>), grid, block, 0, st, a, m);
         return hipGetLastError();
     }
@@ -2259,6 +2259,8 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
 }
 
 }  // namespace
+
+bool select_in_registers(int64_t ld, int r) { return ld <= kFastMaxN && r <= kT; }
 
 int select_split_parts(int64_t B, int64_t ld, int r, int64_t max_blocks) {
     if (B < 1 || ld < 1 || ld > kSplitMaxN || r > kSplitMaxR) return 0;

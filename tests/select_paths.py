@@ -1,53 +1,48 @@
-"""Which select path a batch of few queries on short rows takes: the rules of
-the library's host code, restated for the tests (pinned against the
-workspace size in test_abi_host.py).
+"""How a call runs -- the distance kernel and the select path -- as the library's own host code decides it
+(knnlm_route: no part of the ABI, exported for the tests), under the names that the tests use."""
+import ctypes
+from typing import NamedTuple, Optional
 
-Rows of at most 65536 keys with r <= 1024, whose parts (4096 keys each) over
-all queries fit in 256 workgroups, take the split select.  When the streaming
-distance kernels serve the batch with 16 or 32 key rows per workgroup (each
-of its four waves then records the smallest distance of the 4 or 8 rows it
-took, every fourth row of the tile), a row holds at least 2 r such groups and the finish runs without a
-mixture or in vocabulary slices, the finish reads those group minima and no
-parts kernel runs ("groups"); otherwise a parts kernel samples the row first
-("parts").
-"""
+from paper_2405_19325_amd import _lib
+
+ANY_BYTES = (1 << 64) - 1  # a workspace that holds every list
+
+KERNELS = ("elements", "streaming", "several-queries", "matrix-core", "packed")
+SLICE, SLICED_BLOCKS = 4096, 256  # the sliced finish: vocabulary entries a workgroup, workgroups at most
 
 
-def tile_rows(d: int, esize: int, S: int, max_keys: int) -> int:
-    """Key rows per streaming distance workgroup."""
-    rpt = min((1 << 20) // (d * esize), 4096)
-    rpt = max((rpt + 7) // 8 * 8, 8)
-    while rpt > 16 and S * ((max_keys + rpt - 1) // rpt) < 2048:
-        rpt = (rpt // 2 + 7) // 8 * 8
-    return rpt
+class Route(NamedTuple):
+    kernel: str       # of the distance stage, rows aligned to 16 bytes
+    tile_rows: int
+    queries: int      # per distance workgroup
+    select: str       # see select_path
+    parts: int        # per row (split, wide and sampled selects)
+    group_rows: int   # keys per group where the distance stage writes group minima, else 0
 
 
-def matrix_cores(d: int, esize: int, max_queries: int) -> bool:
-    return esize == 2 and d % 128 == 0 and d <= 65536 and max_queries >= 16
+def sliced(B: int, V: Optional[int]) -> bool:
+    """Whether a split select's finish with a mixture over V tokens (None: no mixture) may read group minima."""
+    return V is None or B * ((V + SLICE - 1) // SLICE) <= SLICED_BLOCKS
 
 
-def group_rows(B: int, d: int, esize: int, S: int, max_keys: int, max_queries: int, r: int) -> int:
-    """Rows per group when the distance stage writes group minima, else 0."""
-    if matrix_cores(d, esize, max_queries):
-        return 0
-    rpt = tile_rows(d, esize, S, max_keys)
-    ld = (max_keys + rpt - 1) // rpt * rpt
-    if ld > 65536 or r > 1024 or B * ((ld + 4095) // 4096) > 256:
-        return 0
-    if rpt not in (16, 32):
-        return 0
-    groups = ld // (rpt // 4)
-    return rpt // 4 if 2 * r <= groups <= 16384 else 0
+def route(B: int, d: int, dtype: int, S: int, max_keys: int, max_queries: int, r: int, V: Optional[int] = None,
+          min_keys: Optional[int] = None, workspace_bytes: int = ANY_BYTES) -> Route:
+    """Of a whole call (V None: no mixture).  select is "fused", "groups" or "parts" (the split select, from group
+    minima or from the parts kernel's sample), "wide", "sampled" or "sampled-16384", "one-workgroup" (the row in
+    registers) or "general" (streamed)."""
+    f = _lib.load()["knnlm_route"]
+    f.restype = None
+    f.argtypes = [ctypes.c_int64] * 6 + [ctypes.c_int, ctypes.c_int32, ctypes.c_size_t, ctypes.c_void_p]
+    out = (ctypes.c_int32 * 8)()
+    f(B, d, S, max_keys if min_keys is None else min_keys, max_keys, max_queries, dtype, r, workspace_bytes, out)
+    kernel, tile, queries, path, parts, group, fused, registers = out
+    select = ("one-workgroup" if registers else "general", "groups" if group and sliced(B, V) else "parts", "wide",
+              "sampled", "sampled-16384")[path]
+    return Route(KERNELS[kernel], tile, queries, "fused" if fused else select, parts, group)
 
 
-def split_path(B: int, d: int, esize: int, S: int, max_keys: int, max_queries: int, r: int, V=None) -> str:
-    """"groups", "parts", "other" (no split select) or "matrix-core" (the split select, if any, samples its
-    rows) for a step with a mixture over V tokens (V None: no mixture)."""
-    if matrix_cores(d, esize, max_queries):
-        return "matrix-core"
-    rpt = tile_rows(d, esize, S, max_keys)
-    ld = (max_keys + rpt - 1) // rpt * rpt
-    if ld > 65536 or r > 1024 or B * ((ld + 4095) // 4096) > 256:
-        return "other"
-    sliced = V is None or B * ((V + 4095) // 4096) <= 256
-    return "groups" if sliced and group_rows(B, d, esize, S, max_keys, max_queries, r) else "parts"
+def of_problem(prob, mixture: bool = True, workspace_bytes: Optional[int] = None) -> Route:
+    """Of a MixtureProblem's calls."""
+    return route(prob.B, prob.d, prob.dtype, prob.S, prob.max_keys, prob.max_queries, prob.r,
+                 prob.V if mixture else None, prob.min_keys,
+                 prob.workspace.numel() if workspace_bytes is None else workspace_bytes)

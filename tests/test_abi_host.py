@@ -183,36 +183,35 @@ def test_packed_dtype_validation(lib):
         INVALID
 
 
-def test_select_path_rules_match_the_workspace_layout(lib):
-    """The tests' restatement of which split rows take the group-minima select
-    (tests/select_paths.py) against the library: the workspace holds B * 4 *
-    tiles fp32 group minima exactly when it says so."""
-    import select_paths
-
-    def ws(**over):
-        return _ws_size(lib, dict(BASE, **over))
+def test_routes_at_the_edges_of_their_rules():
+    """The distance kernel, its tiles and the select path at the sizes where the host code changes them."""
+    from select_paths import route
 
     # decode shape: 32-row tiles, 8192 groups of 8 rows: on for every r <= 1024
-    assert select_paths.group_rows(1, 4096, 2, 1, 65536, 1, 1024) == 8
-    # 4096 keys in 16-row tiles: 1024 groups of 4 rows, so r <= 512
-    small = dict(total_keys=4096, min_keys=4096, max_keys=4096)
-    assert select_paths.tile_rows(4096, 2, 1, 4096) == 16
-    assert select_paths.group_rows(1, 4096, 2, 1, 4096, 1, 512) == 4
-    assert select_paths.group_rows(1, 4096, 2, 1, 4096, 1, 513) == 0
-    assert ws(r=512, **small) - ws(r=513, **small) == 1024 * 4
-    # three queries: three rows of minima
-    assert ws(B=3, max_queries=3, r=512, **small) - ws(B=3, max_queries=3, r=513, **small) == 3 * 1024 * 4
+    assert route(1, 4096, 1, 1, 65536, 1, 1024)[:2] == ("streaming", 32)
+    assert route(1, 4096, 1, 1, 65536, 1, 1024, 32000)[3:] == ("groups", 16, 8)
+    # 4096 keys in 16-row tiles: 1024 groups of 4 rows, so r <= 819 (5/4 r); of the shortest row
+    assert route(1, 4096, 1, 1, 4096, 1, 819, 32000)[3:] == ("groups", 1, 4)
+    assert route(1, 4096, 1, 1, 4096, 1, 820, 32000)[3:] == ("parts", 1, 0)
+    assert route(2, 4096, 1, 2, 4096, 1, 513, 32000, min_keys=2564)[3:] == ("parts", 1, 0)
+    assert route(2, 4096, 1, 2, 4096, 1, 513, 32000, min_keys=2568)[3:] == ("groups", 1, 4)
+    # a vocabulary of more slices than the chip takes at once: no group minima
+    assert route(2, 16, 0, 1, 40000, 2, 1024, 600001).select == "parts"
+    assert route(2, 16, 0, 1, 40000, 2, 1024).select == "groups"
     # 16 bf16 queries on a set take the matrix cores: no group minima
-    assert select_paths.group_rows(16, 4096, 2, 1, 4096, 16, 512) == 0
-    assert ws(B=16, max_queries=16, r=512, **small) == ws(B=16, max_queries=16, r=513, **small)
-    # fp32 keys of width 16 on 40,000-key rows: 16-row tiles, 10,000 groups of 4
-    assert select_paths.tile_rows(16, 4, 1, 40000) == 16
-    assert select_paths.group_rows(1, 16, 4, 1, 40000, 1, 1024) == 4
+    assert route(16, 4096, 1, 1, 4096, 16, 512)[3:] == ("parts", 1, 0)
     # 64-row tiles (many sets): the parts kernel samples the rows
-    many = dict(B=32, S=32, d=256, total_keys=32 * 4096, min_keys=4096, max_keys=4096, max_queries=1, r=256)
-    assert select_paths.tile_rows(256, 2, 32, 4096) == 64
-    assert select_paths.split_path(32, 256, 2, 32, 4096, 1, 256, V=32000) == "parts"
-    assert ws(**many) == ws(**dict(many, r=255))
+    assert route(32, 256, 1, 32, 4096, 1, 256, 32000)[1:] == (64, 1, "parts", 1, 0)
+    # 1024 parts over all rows, then one workgroup a row of the sampled select; r = 1024 is the split select's most
+    assert route(64, 16, 0, 1, 65536, 64, 1024, 32000)[3:5] == ("parts", 16)
+    assert route(65, 16, 0, 1, 65536, 65, 1024, 32000)[3:5] == ("sampled", 4)
+    assert route(3, 16, 0, 1, 40000, 3, 1025).select == "sampled"
+    assert route(3, 16, 0, 1, 40000, 3, 2049).select == "general"
+    # a workspace that holds no lists: one workgroup a row
+    assert route(65, 16, 0, 1, 65536, 65, 1024, workspace_bytes=0).select == "one-workgroup"
+    assert route(17, 16, 0, 1, 65536, 17, 1024, workspace_bytes=0).select == "one-workgroup"
+    assert route(16, 16, 0, 1, 65536, 16, 1024, workspace_bytes=0).select == "groups"
+    assert route(3, 16, 0, 1, 40000, 3, 2048, workspace_bytes=0).select == "general"
 
 
 def test_least_workspace_is_that_of_whole_tiles(lib):

@@ -77,7 +77,8 @@ def _problem(q, k, vals, p_lm, ko, qo, r, mu, lam, dtype):
 
 def _path(q, k, ko, qo, r, V, esize):
     sizes, qps = np.diff(ko), np.diff(qo)
-    return select_paths.split_path(q.shape[0], k.shape[1], esize, len(sizes), int(sizes.max()), int(qps.max()), r, V)
+    return select_paths.route(q.shape[0], k.shape[1], 0 if esize == 4 else 1, len(sizes), int(sizes.max()),
+                              int(qps.max()), r, V, int(sizes[qps > 0].min()))
 
 
 def _check_select(ids, dists, o_ids, o_d):
@@ -141,8 +142,8 @@ def test_group_select_exact_integers(name, sizes, qps, d, r, V, gr, dtype):
     _say(f"group-minima select {name} {dtype}")
     esize = 4 if dtype == torch.float32 else 2
     rng, q, k, vals, p_lm, ko, qo = _store(sizes, qps, d, V, 300 + r + d)
-    assert _path(q, k, ko, qo, r, V, esize) == "groups"
-    assert select_paths.group_rows(q.shape[0], d, esize, len(sizes), max(sizes), max(qps), r) == gr
+    path = _path(q, k, ko, qo, r, V, esize)
+    assert path.select == "groups" and path.group_rows == gr
     n = k.shape[0]
     # a third of the keys and two whole runs of 64 rows (every group in them) masked
     masked = np.union1d(rng.choice(n, n // 3, replace=False), np.r_[128:192, ko[1] - 64:ko[1]])
@@ -163,7 +164,7 @@ def test_group_select_planted_neighbours(layout):
     else:  # rows 32 t + 9 i, i < 4: one in each of the four groups of every 32-row tile
         near = (32 * np.arange(n // 32)[:, None] + 9 * np.arange(4)).ravel()
     k[near, :3] = rng.integers(-20, 21, (near.size, 3))
-    assert _path(q, k, ko, qo, r, V, 4) == "groups"
+    assert _path(q, k, ko, qo, r, V, 4).select == "groups"
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, 0.4, torch.float32)
     _check_all_modes(prob, q, k, vals, p_lm, ko, qo, r, 0.05, 0.4)
     if layout == "nearest-in-few-groups":
@@ -178,7 +179,7 @@ def test_group_select_all_keys_equal_falls_back():
     rng, q, k, vals, p_lm, ko, qo = _store((n,), (2,), d, V, 322)
     k[:] = 0.0
     k[:, 0] = 3.0
-    assert _path(q, k, ko, qo, r, V, 4) == "groups"
+    assert _path(q, k, ko, qo, r, V, 4).select == "groups"
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, 0.4, torch.float32)
     _check_all_modes(prob, q, k, vals, p_lm, ko, qo, r, 0.05, 0.4)
     assert prob.ids.cpu().numpy()[0].tolist() == list(range(r))
@@ -190,8 +191,8 @@ def test_group_minima_and_parts_kernel_agree():
     _say("group minima vs parts kernel")
     sizes, qps, d, r, V = (40001, 33333), (2, 1), 16, 1024, 600001
     rng, q, k, vals, p_lm, ko, qo = _store(sizes, qps, d, V, 323)
-    assert _path(q, k, ko, qo, r, V, 4) == "parts"
-    assert _path(q, k, ko, qo, r, None, 4) == "groups"
+    assert _path(q, k, ko, qo, r, V, 4).select == "parts"
+    assert _path(q, k, ko, qo, r, None, 4).select == "groups"
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, 0.4, torch.float32)
     o_ids, o_d = oracle.select(q, k, "f32", ko, qo, r)
     prob.run_part("distances")
@@ -215,7 +216,7 @@ def test_sliced_finish_sums_are_exact(path):
         sizes, qps, d, r, V = (4096,) * 32, (1,) * 32, 256, 256, 32000
     rng, q, k, vals, p_lm, ko, qo = _store(sizes, qps, d, V, 324)
     vals = np.minimum(rng.zipf(1.1, vals.size) - 1, V - 1).astype(np.int32)
-    assert _path(q, k, ko, qo, r, V, 4) == path
+    assert _path(q, k, ko, qo, r, V, 4).select == path
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, 0.4, torch.float32)
     first = [t.clone() for t in prob.run()]
     for _ in range(3):

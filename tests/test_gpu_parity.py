@@ -424,7 +424,7 @@ SAMPLED_PATHS = [("parts", 2, 600001), ("groups", 1, 50), ("one-workgroup", 20, 
 
 def _check_path(path, B, n, d, r, V):
     if path != "one-workgroup":
-        assert select_paths.split_path(B, d, 2, 1, n, B, r, V) == path
+        assert select_paths.route(B, d, 1, 1, n, B, r, V).select == path
 
 
 @pytest.mark.parametrize("path,B,V", SAMPLED_PATHS, ids=[c[0] for c in SAMPLED_PATHS])
@@ -532,7 +532,7 @@ def test_split_select_sliced_finish_exact_integers(case, V, rrc, layout):
         q[:, :3] = rng.integers(-30, 31, (B, 3))
         q[:, 3] = np.arange(B) % 5
     sizes = np.diff(ko)
-    assert select_paths.split_path(B, d, 4, len(sizes), int(sizes.max()), int(np.diff(qo).max()), r, V) == (
+    assert select_paths.route(B, d, 0, len(sizes), int(sizes.max()), int(np.diff(qo).max()), r, V).select == (
         "groups" if layout == "one-set" else "parts")
     k = np.zeros((n, d), np.float32)
     if case != "all-equal":
