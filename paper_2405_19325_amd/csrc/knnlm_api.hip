@@ -57,7 +57,7 @@ bool fused_shape(int64_t B, int64_t d, knn_dtype dtype, int64_t max_queries, int
 }
 
 Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64_t max_queries, knn_dtype dtype,
-                 int32_t r, int rows_per_tile, bool roomy) {
+                 int32_t r, int rows_per_tile, bool roomy, bool may_fuse = true) {
     Layout L{};
     L.rows_per_tile = rows_per_tile;
     L.tiles_per_set = (max_keys + L.rows_per_tile - 1) / L.rows_per_tile;
@@ -82,7 +82,7 @@ Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64
     L.off_best = align_up(L.off_thr + sizeof(uint32_t) * per_row);
     L.off_ticket = align_up(L.off_best + sizeof(uint64_t) * per_row);
     L.off_fallback = align_up(L.off_ticket + sizeof(uint32_t) * per_row);
-    L.fused = fused_shape(B, d, dtype, max_queries, L.ld, r, L.tiles_per_set);
+    L.fused = may_fuse && fused_shape(B, d, dtype, max_queries, L.ld, r, L.tiles_per_set);
     const FusedSample sample = fused_sample(L.rows_per_tile);
     L.sample_rows = sample.rows;
     L.sample_every = sample.every;
@@ -102,13 +102,16 @@ Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64
 // static scratch array, and callers with a workspace of that size).
 // Roomy layouts of query batches on row-major keys take finer tiles where the
 // launch would leave CUs idle (mfma_fine_rows), except where the fused select
-// runs: its sample is laid out in whole tiles.
+// runs on the coarse ones.  Finer tiles don't bring the fused select to shorter
+// rows: its sample has too few pieces there (128 queries on 70,000 keys of d =
+// 1024, r = 64, a step: 190 us fused over 256-row tiles, 81 us by the wide select
+// over 128-row ones; 156 us over the coarse ones).
 Layout layout(int64_t B, int64_t d, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries, knn_dtype dtype,
               bool packed, int32_t r, size_t bytes) {
     const int rows = dist_tile_rows(d, dtype, S, max_keys, max_queries);
     Layout L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, true);
     if (!packed && !L.fused && mfma_shape(d, dtype, max_queries))
-        L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, mfma_fine_rows(rows, S, max_keys, max_queries), true);
+        L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, mfma_fine_rows(rows, S, max_keys, max_queries), true, false);
     return L.total <= bytes ? L : layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, false);
 }
 

@@ -433,9 +433,8 @@ int mfma_tile_rows(int64_t d) {
 }
 
 // Finer tiles where those of `rows` would leave CUs idle.  Two or three
-// workgroups share a CU, so tiles are halved (down to one 128-key pass; 256
-// rows for 128-query groups on the long rows that the fused select may take)
-// while they are fewer than four for each CU; and where 64-row or 32-row tiles
+// workgroups share a CU, so tiles are halved (down to one 128-key pass) while
+// they are fewer than four for each CU; and where 64-row or 32-row tiles
 // still fit one a CU (two a CU for up to 32 queries at 64 rows: there the queries' share of
 // the loads is small), each workgroup's few keys are all in flight at once.
 // Measured at d = 4096, 128 / 64 / 32 rows a tile: 7,000 keys, 30 queries 33 / 22
@@ -447,9 +446,8 @@ int mfma_fine_rows(int rows, int64_t S, int64_t max_keys, int64_t max_queries) {
     const int64_t groups = (max_queries + 127) / 128;
     auto blocks = [&](int64_t n) { return S * ((max_keys + n - 1) / n) * groups; };
     if (S >= 4 * kCus) return rows;
-    const int64_t least = max_queries > 64 && max_keys > 65536 ? 256 : 128;
     int64_t n = rows;
-    while (n > least && blocks(n) < 4 * kCus) n = (n / 2 + least - 1) / least * least;
+    while (n > 128 && blocks(n) < 4 * kCus) n = (n / 2 + 127) / 128 * 128;
     if (n > 128) return static_cast<int>(n);
     if (blocks(32) <= kCus) return 32;
     if (blocks(64) <= (max_queries <= 32 ? 2 * kCus : kCus)) return 64;

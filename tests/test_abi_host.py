@@ -207,6 +207,12 @@ def test_routes_at_the_edges_of_their_rules():
     assert route(65, 16, 0, 1, 65536, 65, 1024, 32000)[3:5] == ("sampled", 4)
     assert route(3, 16, 0, 1, 40000, 3, 1025).select == "sampled"
     assert route(3, 16, 0, 1, 40000, 3, 2049).select == "general"
+    # 128-query batches on long rows: fused where the rows hold 2 r coarse tiles (1024 rows at d = 1024, 256 at
+    # d = 4096), which the finer tiles of shorter rows don't count for
+    assert route(128, 1024, 2, 1, 131072, 128, 64)[1::2] == (1024, "fused", 0)
+    assert route(128, 1024, 2, 1, 130048, 128, 64)[1::2] == (128, "wide", 0)
+    assert route(128, 4096, 1, 1, 65800, 128, 64)[1::2] == (256, "fused", 0)
+    assert route(128, 128, 1, 1, 65800, 128, 64).select != "fused"
     # a workspace that holds no lists: one workgroup a row
     assert route(65, 16, 0, 1, 65536, 65, 1024, workspace_bytes=0).select == "one-workgroup"
     assert route(17, 16, 0, 1, 65536, 17, 1024, workspace_bytes=0).select == "one-workgroup"

@@ -16,6 +16,7 @@ import pytest
 import torch
 
 import oracle
+import select_paths
 from workloads import gen  # noqa: F401  (keeps the import order of the other GPU modules)
 
 pytestmark = pytest.mark.gpu
@@ -139,27 +140,28 @@ def test_fused_nest_step_with_masked_keys(layout):
 # a last tile of 8, 119 or 256 rows.
 @pytest.mark.parametrize("sizes", [(65536 + 100,), (65800,), (65792 + 119,), (66048,), (70001, 65800)],
                          ids=lambda s: "-".join(map(str, s)))
-@pytest.mark.parametrize("d,queries", [(128, 66), (1024, 128)])
+@pytest.mark.parametrize("d,queries", [(4096, 66), (8192, 128)])
 def test_fused_select_of_wholly_sampled_tiles(d, queries, sizes):
     """Tiles of 256 rows, as large as the sample's pieces: the listing pass has nothing to take of a sampled one."""
     _say(f"fused select, 256-row tiles: d={d} {sizes}")
     rng = np.random.default_rng(d + sum(sizes))
     n, B, V = sum(sizes), queries * len(sizes), 500
-    k, q = np.zeros((n, d), np.float32), np.zeros((B, d), np.float32)
-    k[:, :8], q[:, :8] = rng.integers(-30, 31, (n, 8)), rng.integers(-30, 31, (B, 8))
+    k, q = rng.integers(-30, 31, (n, 8)).astype(np.float32), rng.integers(-30, 31, (B, 8)).astype(np.float32)
     vals = rng.integers(0, V, n).astype(np.int32)
     p_lm = rng.dirichlet(np.ones(V), B).astype(np.float32)
     ko = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     qo = np.arange(len(sizes) + 1, dtype=np.int64) * queries
     dev = "cuda"
-    tk, tq = (torch.as_tensor(x, device=dev).to(torch.bfloat16) for x in (k, q))
+    tk, tq = (torch.zeros(x.shape[0], d, dtype=torch.bfloat16, device=dev) for x in (k, q))
+    for t, x in ((tk, k), (tq, q)):
+        t[:, :8] = torch.as_tensor(x, device=dev)  # the other entries stay 0
     prob = knn.MixtureProblem(tq, tk, torch.as_tensor(vals, device=dev), torch.as_tensor(ko, device=dev),
                               torch.as_tensor(qo, device=dev), torch.as_tensor(p_lm, device=dev), R, 0.01, 0.3,
                               key_offsets_host=ko, query_offsets_host=qo)
+    assert select_paths.of_problem(prob)[1::2] == (256, "fused", 0)
     p_m, ids, dists = prob.run()
     torch.cuda.synchronize()
-    # (the entries past the eighth are 0)
-    o_ids, o_d = oracle.select(np.ascontiguousarray(q[:, :8]), np.ascontiguousarray(k[:, :8]), "f32", ko, qo, R)
+    o_ids, o_d = oracle.select(q, k, "f32", ko, qo, R)
     np.testing.assert_array_equal(ids.cpu().numpy(), o_ids)
     np.testing.assert_array_equal(dists.cpu().numpy().astype(np.float64), o_d)
     np.testing.assert_allclose(p_m.cpu().numpy(), oracle.mix(o_ids, o_d, vals, ko, qo, p_lm, 0.01, 0.3),
@@ -182,6 +184,7 @@ def test_fused_select_of_tiles_off_a_power_of_two(layout):
     prob = knn.MixtureProblem(tq, tk, values, torch.as_tensor(ko, device=dev), torch.as_tensor(qo, device=dev), p_lm,
                               r, 0.01, key_offsets_host=ko, query_offsets_host=qo,
                               packed_keys=knn.pack_keys(tk) if layout == "packed" else None)
+    assert select_paths.of_problem(prob)[1::2] == (2816, "fused", 0)
     _, ids, dists = prob.run()
     o_ids, o_d = oracle.select(np.ascontiguousarray(q[:, :8]), np.ascontiguousarray(k[:, :8]), "f32", ko, qo, r)
     np.testing.assert_array_equal(ids.cpu().numpy(), o_ids)
