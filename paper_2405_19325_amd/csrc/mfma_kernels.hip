@@ -373,9 +373,13 @@ __global__ __launch_bounds__(WK * WQ * kWave, 2) void k_dist_mfma(DistArgs a, in
 // the small ones; then more of d per step, since a step's latency and not its
 // bytes is what takes the time).  Measured on bf16 keys of d = 4096, 8 x 65,536
 // keys: 16 queries 746 us (64-key passes of 128 elements 765 us), 32 queries
-// 804 us (64 keys, 4 buffers: 815 us), 64 queries 905 us (64 keys, 4 buffers: 955 us);
-// 128 queries on 4 x 65,536 keys of d = 2048: 306 us (256 keys, 3 buffers: 299 us, but
-// 81 against 48 us on one set of 7,000 keys).
+// 804 us (64 keys, 4 buffers: 815 us), 64 queries 905 us (64 keys, 4 buffers: 955 us).
+// 128-query groups on tiles of whole 256-row passes take those: a pass stages
+// the 128 query rows anew, so half as many passes load a quarter less.  256- and
+// 128-key passes (four buffers), f16: 8.4 M keys of d = 1024, fused, 3.81 and 4.19
+// ms (2 x 4 wave groups, which read more of LDS, 4.01 ms); 2 x 262,144 keys of d =
+// 4096 0.99 and 1.06 ms; 100 queries on each of 50 sets of 20,000 keys of d = 128,
+// whose passes have two steps, 199 and 203 us.
 template <knn_dtype DT, int MQ, int WK, int WQ, int NB, bool NORMS, int PK, int SPAN, int FM = 0>
 hipError_t launch_one(const DistArgs &a, int64_t n_tiles, int64_t groups, dim3 grid, hipStream_t st) {
     hipLaunchKernelGGL((k_dist_mfma<DT, MQ, WK, WQ, NB, NORMS, PK, SPAN, FM>), grid, dim3(WK * WQ * kWave), 0, st, a,
@@ -388,8 +392,8 @@ hipError_t launch_mq(int mq, const DistArgs &a, int64_t n_tiles, int64_t groups,
                      int fm) {
     if (fm != 0) {  // the fused select: 128-query workgroups only
         if (mq != 8) return hipErrorInvalidValue;
-        if (fm == 1) return launch_one<DT, 8, 2, 4, 4, NORMS, 128, 64, 1>(a, n_tiles, groups, grid, st);
-        return launch_one<DT, 8, 2, 4, 4, NORMS, 128, 64, 2>(a, n_tiles, groups, grid, st);
+        if (fm == 1) return launch_one<DT, 8, 4, 2, 3, NORMS, 256, 64, 1>(a, n_tiles, groups, grid, st);
+        return launch_one<DT, 8, 4, 2, 3, NORMS, 256, 64, 2>(a, n_tiles, groups, grid, st);
     }
     const int tile = a.rows_per_tile;
     switch (mq) {
@@ -408,6 +412,7 @@ hipError_t launch_mq(int mq, const DistArgs &a, int64_t n_tiles, int64_t groups,
     case 8:
         if (tile == 32) return launch_one<DT, 8, 2, 4, 3, NORMS, 32, 128>(a, n_tiles, groups, grid, st);
         if (tile == 64) return launch_one<DT, 8, 2, 4, 4, NORMS, 64, 64>(a, n_tiles, groups, grid, st);
+        if (tile % 256 == 0) return launch_one<DT, 8, 4, 2, 3, NORMS, 256, 64>(a, n_tiles, groups, grid, st);
         return launch_one<DT, 8, 2, 4, 4, NORMS, 128, 64>(a, n_tiles, groups, grid, st);
     default: return hipErrorInvalidValue;
     }
@@ -434,9 +439,12 @@ int mfma_tile_rows(int64_t d) {
 
 // Finer tiles where those of `rows` would leave CUs idle.  Two or three
 // workgroups share a CU, so tiles are halved (down to one 128-key pass) while
-// they are fewer than four for each CU; and where 64-row or 32-row tiles
-// still fit one a CU (two a CU for up to 32 queries at 64 rows: there the queries' share of
-// the loads is small), each workgroup's few keys are all in flight at once.
+// they are fewer than four for each CU, or three for 128-query groups, which have
+// a CU to themselves (two / three / four for each CU: 25 sets of 20,000 keys of d =
+// 1024 and 100 queries 272 / 271 / 289 us, 8 sets of 70,000 keys and 128 queries 378
+// / 335 / 336 us).  Where 64-row or 32-row tiles still fit one a CU (two a CU for
+// up to 32 queries at 64 rows: there the queries' share of the loads is small),
+// each workgroup's few keys are all in flight at once.
 // Measured at d = 4096, 128 / 64 / 32 rows a tile: 7,000 keys, 30 queries 33 / 22
 // / 17 us (256 rows 72 us); 2 x 7,000 keys, 16 queries 30 / 25 / 28 us; 4 x 7,000
 // keys, 32 queries 53 / 49 / 61 us, 64 queries 56 / 63 / 84 us; 8 sets of 4,000 to
@@ -447,7 +455,7 @@ int mfma_fine_rows(int rows, int64_t S, int64_t max_keys, int64_t max_queries) {
     auto blocks = [&](int64_t n) { return S * ((max_keys + n - 1) / n) * groups; };
     if (S >= 4 * kCus) return rows;
     int64_t n = rows;
-    while (n > 128 && blocks(n) < 4 * kCus) n = (n / 2 + 127) / 128 * 128;
+    while (n > 128 && blocks(n) < (max_queries > 64 ? 3 : 4) * kCus) n = (n / 2 + 127) / 128 * 128;
     if (n > 128) return static_cast<int>(n);
     if (blocks(32) <= kCus) return 32;
     if (blocks(64) <= (max_queries <= 32 ? 2 * kCus : kCus)) return 64;

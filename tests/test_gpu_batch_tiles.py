@@ -8,6 +8,8 @@ import numpy as np
 import pytest
 import torch
 
+import select_paths
+
 pytestmark = pytest.mark.gpu
 
 knn = pytest.importorskip("paper_2405_19325_amd")
@@ -60,6 +62,23 @@ def test_bits_of_the_packed_kernel(q, sizes, d, norms):
     for name in ("ids", "dists", "lambdas"):
         assert torch.equal(outs[0][name], outs[1][name]), name
     torch.testing.assert_close(outs[0]["p_m"], outs[1]["p_m"], rtol=1e-5, atol=1e-8)
+
+
+# Stores large enough for tiles of whole 256-row passes, which groups of more than 64 queries take: 4 to 20 steps a
+# tile (the step count padded to a multiple of three by 0, 1 and 2), one pass a tile and several, two query groups.
+@pytest.mark.parametrize("norms", [False, True], ids=["own-norms", "given-norms"])
+@pytest.mark.parametrize("q,S,n,d", [(100, 4, 66001, 256), (128, 3, 66057, 384), (70, 20, 20001, 128),
+                                     (130, 3, 40003, 640), (66, 1, 300100, 512)])
+def test_bits_of_the_packed_kernel_in_256_row_passes(q, S, n, d, norms):
+    print(f"[gpu] 256-row passes q={q} S={S} n={n} d={d} norms={norms}", flush=True)
+    assert select_paths.route(q * S, d, 2, S, n, q, 64).tile_rows % 256 == 0
+    g = torch.Generator(device="cuda").manual_seed(q + d)
+    ko, qo = np.arange(S + 1, dtype=np.int64) * n, np.arange(S + 1, dtype=np.int64) * q
+    k, x = ((torch.randn((m, d), generator=g, device="cuda") * (8 / math.sqrt(d))).half() for m in (S * n, S * q))
+    args = dict(key_sqnorms=knn.key_sqnorms(k) if norms else None, key_offsets_host=ko, query_offsets_host=qo)
+    tko, tqo = torch.from_numpy(ko).cuda(), torch.from_numpy(qo).cuda()
+    one, two = (knn.distances(x, k, tko, tqo, packed_keys=p, **args) for p in (None, knn.pack_keys(k)))
+    assert torch.equal(one.view(torch.int32), two.view(torch.int32))
 
 
 def test_workspace_of_both_key_layouts():
