@@ -718,24 +718,30 @@ int knn_abi_version(void) { return KNNLM_ABI_VERSION; }
 
 /* How a call of these sizes runs on a workspace of so many bytes, for the tests
  * (no part of the ABI, not in knnlm.h): the distance kernel (0 elements, 1
- * streaming, 2 several queries, 3 matrix cores, 4 packed keys; of 16-byte
- * aligned rows), its rows per tile, queries per workgroup, the select path (SelectPath), its
- * parts per row, rows per key group (0: no group minima), whether the fused
- * select runs, and whether rows selected by one workgroup do so in registers. */
-void knnlm_route(int64_t B, int64_t d, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries,
-                 knn_dtype dtype, int32_t r, size_t workspace_bytes, int32_t *out) {
+ * streaming, 2 several queries, 3 matrix cores, 4 packed keys; of rows aligned to 16
+ * bytes), its rows per tile, its queries per workgroup, the select
+ * (SelectRoute::Kind) with a mixture of `mode` (MixMode) over V tokens, its
+ * parts per row, rows per key group (0: no group minima), and whether the
+ * fused select runs. */
+void knnlm_route(int64_t B, int64_t d, int64_t V, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries,
+                 knn_dtype dtype, int32_t r, int mode, size_t workspace_bytes, int32_t *out) {
     const knn_dtype et = base_dtype(dtype);
     const bool packed = packed_flag(dtype);
     const Layout L = layout(B, d, S, min_keys, max_keys, max_queries, et, packed, r, workspace_bytes);
     const DistPlan p = plan_distances(d, et, S, max_keys, max_queries, nullptr, nullptr);
+    SelectArgs a{};
+    a.path = L.path;
+    a.parts = L.split_parts;
+    a.ld = L.ld;
+    a.r = r;
+    a.group_rows = L.group_rows;
     out[0] = p.mfma ? (packed ? 4 : 3) : p.multi ? 2 : p.vec ? 1 : 0;
     out[1] = L.rows_per_tile;
     out[2] = p.nq;
-    out[3] = L.path;
+    out[3] = select_route(a, B, static_cast<MixMode>(mode), mode == kNoMix ? 0 : V, true).kind;
     out[4] = L.split_parts;
     out[5] = L.group_rows;
     out[6] = L.fused;
-    out[7] = L.path == kRowSelect && select_in_registers(L.ld, r);
 }
 
 }  // extern "C"

@@ -14,6 +14,8 @@ enum SelectPath {
     kSampled4Select   // the same from 16384
 };
 
+enum MixMode { kNoMix = 0, kMixFixed = 1, kMixRrc = 2, kMixNest = 3 };
+
 struct SelectArgs {
     SelectPath path;
     int parts;                   // parts per row (split, wide and sampled paths)
@@ -97,6 +99,16 @@ hipError_t launch_spec_verify(const float *p_max, const float *p_draft, const in
 int select_capacity(int r);
 // Whether the select of one workgroup a row holds the row in registers.
 bool select_in_registers(int64_t ld, int r);
+// What a select of one mode (V: 0 without a mixture) launches: the layout's
+// path, or one workgroup a row in registers where that is the faster.
+struct SelectRoute {
+    enum Kind { kGroups, kParts, kWide, kSampled, kSampled4, kRegisters, kStreamed } kind;
+    int64_t slices;  // of a row in the split finish (0: whole rows)
+};
+SelectRoute select_route(const SelectArgs &a, int64_t B, MixMode mode, int64_t V, bool nest_words);
+constexpr int64_t kChipCus = 256;
+constexpr int64_t kRegisterKeys = 32768;
+constexpr int64_t kLargeVocab = 16384;
 // Split select: rows of at most kSplitMaxN keys are cut into parts of
 // kSplitKeys keys, one workgroup each, when r <= kSplitMaxR and there are at
 // most max_blocks parts over all queries (two passes of the chip.  184 rows of
@@ -135,7 +147,10 @@ int select_wide_parts(int64_t B, int64_t ld, int r, int64_t tiles_per_set);
 // path.  The streamed select of one workgroup a row, which it replaces, passes
 // over the row three times or more: 128 rows of 262,144 keys 141 us, 96 us so;
 // 463 rows of 185,000 to 245,000 keys 335 and 215 us; 278 rows of 8,500 keys,
-// r = 2048, 128 and 59 us.
+// r = 2048, 128 and 59 us.  Rows that fit the registers are read once there:
+// up to 32768 keys the sampled select is ahead or level (2,000 rows of 12,000 keys,
+// r = 1024, V = 8000: 0.77 of the time; of 32,000 keys 0.88), longer ones are not sampled
+// (200 rows of 48,000 keys, V = 32000: 43 us, 33 us in registers; 600 rows 1.0 of the time).
 // Its lists (32 KiB each) stay under 128 MiB, or under the distances: 100,000
 // rows of 1,000 keys would need 3 GiB of them beside 0.8 GiB of the rest.
 constexpr int64_t kSampledMaxLists = 4096;

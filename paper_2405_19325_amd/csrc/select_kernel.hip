@@ -70,7 +70,6 @@ __device__ float4 g_mix_sink;
 // the mixture with lambda_t from relative retrieval confidence, or that and
 // the decoding outputs of a NEST step (greedy token, span start, draft
 // probability).
-enum MixMode { kNoMix = 0, kMixFixed = 1, kMixRrc = 2, kMixNest = 3 };
 constexpr bool rrc_mode(int mode) { return mode == kMixRrc || mode == kMixNest; }
 
 struct Shared {
@@ -2184,17 +2183,15 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
     if (a.tile_min == nullptr || a.tile_max == nullptr) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(B)), block(kT);
     const int parts = a.parts;
-    if (a.path == kSplitSelect) {
+    constexpr bool MIX = MODE != kNoMix;
+    const SelectRoute route = select_route(a, B, static_cast<MixMode>(MODE), MIX ? m.V : 0,
+                                           m.best != nullptr && m.ticket != nullptr);
+    if (route.kind == SelectRoute::kGroups || route.kind == SelectRoute::kParts) {
         if (a.cand == nullptr || a.part_count == nullptr || a.part_thr == nullptr) return hipErrorInvalidValue;
-        // With mixing and few rows, the finish runs once per vocabulary slice
-        // of each row, every one of those workgroups selecting pi again, so
-        // that the row is written by many CUs.
-        constexpr bool MIX = MODE != kNoMix;
-        const int64_t slices = MIX ? (m.V + kVocabSlice - 1) / kVocabSlice : 1;
-        const bool sliced = MIX && B * slices <= kSliceMaxBlocks &&
-                            (MODE != kMixNest || (m.best != nullptr && m.ticket != nullptr));
-        if (a.group_min != nullptr && (!MIX || sliced)) {  // no parts kernel: the finish reads the group minima
-            if (a.group_rows != 4 && a.group_rows != 8) return hipErrorInvalidValue;
+        const int64_t slices = route.slices;
+        const bool sliced = slices > 0;
+        if (route.kind == SelectRoute::kGroups) {  // no parts kernel: the finish reads the group minima
+            if (a.group_min == nullptr || (a.group_rows != 4 && a.group_rows != 8)) return hipErrorInvalidValue;
             if (a.groups_per_set % 4 != 0 || a.groups_per_set > kGroupMaxPerRow) return hipErrorInvalidValue;
             const bool wide = a.groups_per_set > 2 * 4 * kT;  // more than two 16-byte words of minima per thread
             if constexpr (MIX) {
@@ -2234,18 +2231,18 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
         hipLaunchKernelGGL((k_select_finish<MODE, false, false>), grid, block, 0, st, a, m, parts, 1);
         return hipGetLastError();
     }
-    if (a.path == kWideSelect || a.path == kSampledSelect || a.path == kSampled4Select) {
+    if (route.kind == SelectRoute::kWide || route.kind == SelectRoute::kSampled || route.kind == SelectRoute::kSampled4) {
         if (a.cand == nullptr || a.part_count == nullptr || a.part_thr == nullptr) return hipErrorInvalidValue;
         const dim3 pgrid(static_cast<unsigned>(B * parts));
-        if (a.path == kWideSelect) hipLaunchKernelGGL(k_select_wide_parts<0>, pgrid, block, 0, st, a, parts);
-        else if (a.path == kSampledSelect) hipLaunchKernelGGL(k_select_wide_parts<1>, pgrid, block, 0, st, a, parts);
+        if (route.kind == SelectRoute::kWide) hipLaunchKernelGGL(k_select_wide_parts<0>, pgrid, block, 0, st, a, parts);
+        else if (route.kind == SelectRoute::kSampled) hipLaunchKernelGGL(k_select_wide_parts<1>, pgrid, block, 0, st, a, parts);
         else hipLaunchKernelGGL(k_select_wide_parts<4>, pgrid, block, 0, st, a, parts);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_select_wide_finish<MODE>), grid, block, 0, st, a, m, parts);
         return hipGetLastError();
     }
-    if (select_in_registers(a.ld, a.r)) {
+    if (route.kind == SelectRoute::kRegisters) {
         hipLaunchKernelGGL((k_select_fast<MODE>), grid, block, 0, st, a, m);
         return hipGetLastError();
     }
@@ -2261,6 +2258,39 @@ hipError_t launch_sel(const SelectArgs &a, const MixArgs &m, int64_t B, hipStrea
 }  // namespace
 
 bool select_in_registers(int64_t ld, int r) { return ld <= kFastMaxN && r <= kT; }
+
+SelectRoute select_route(const SelectArgs &a, int64_t B, MixMode mode, int64_t V, bool nest_words) {
+    const SelectRoute one{select_in_registers(a.ld, a.r) ? SelectRoute::kRegisters : SelectRoute::kStreamed, 0};
+    switch (a.path) {
+    case kRowSelect: return one;
+    case kWideSelect: return {SelectRoute::kWide, 0};
+    case kSampledSelect:
+    case kSampled4Select:
+        // Rows of at most a part's keys: every key is listed and sorted, and the finish writes a large vocabulary
+        // one tile after the other.  2,000 rows of 3,000 keys, V = 32000, r = 64: 314 us, 227 us
+        // in registers; V = 50257, r = 1024: 512 and 497 us; V = 1000: 95 and 104 us.
+        if (a.ld <= kSplitKeys && V > kLargeVocab && one.kind == SelectRoute::kRegisters) return one;
+        return {a.path == kSampledSelect ? SelectRoute::kSampled : SelectRoute::kSampled4, 0};
+    case kSplitSelect: break;
+    }
+    // With mixing and few rows, the finish runs once per vocabulary slice
+    // of each row, every one of those workgroups selecting pi again, so
+    // that the row is written by many CUs.
+    const int64_t slices = (V + kVocabSlice - 1) / kVocabSlice;
+    const bool sliced = mode != kNoMix && B * slices <= kSliceMaxBlocks && (mode != kMixNest || nest_words);
+    if (a.group_rows > 0 && (mode == kNoMix || sliced)) return {SelectRoute::kGroups, sliced ? slices : 0};
+    // Over two parts for each CU, but no more rows than CUs, of at most 32768
+    // keys: one workgroup a row takes one pass of the chip, the parts a second one.  100
+    // rows of 32,000 keys, r = 1024, V = 32000: 35.6 us, 30.4 us in registers (61 and 43 us with the distances
+    // out of cache); 200 of 12,000: 31.0 and 27.6 us.  Longer rows: 50 of 65,000 keys 32.4 and 33.6 us.
+    const int64_t blocks = B * a.parts;
+    if (blocks > 2 * kChipCus && B <= kChipCus && a.ld <= kRegisterKeys) return one;
+    // Fixed lambda, rows of one part and a large vocabulary, whose dense term
+    // that one part then writes alone: 1,000 rows of 3,000 keys, r = 1024, V = 32000: 255 us, 213 us in
+    // registers; V = 1000: 66 and 78 us.  (lambda_t: the finish writes the row; 214 and 210 us.)
+    if (mode == kMixFixed && !sliced && a.parts == 1 && B > kChipCus && V > kLargeVocab) return one;
+    return {SelectRoute::kParts, sliced ? slices : 0};
+}
 
 int select_split_parts(int64_t B, int64_t ld, int r, int64_t max_blocks) {
     if (B < 1 || ld < 1 || ld > kSplitMaxN || r > kSplitMaxR) return 0;
@@ -2295,6 +2325,7 @@ int select_wide_parts(int64_t B, int64_t ld, int r, int64_t tiles_per_set) {
 
 int select_sampled_parts(int64_t B, int64_t ld, int r, SelectPath &path) {
     if (B < 1 || ld < 1 || ld > 0x7fffffffLL || r > kWideMaxR) return 0;
+    if (select_in_registers(ld, r) && ld > kRegisterKeys) return 0;
     for (int u = 1; u <= 4; u += 3) {
         const int M = 4 * kT * u;
         const float ks = static_cast<float>(sample_rank(static_cast<uint32_t>(r), M, static_cast<float>(ld)));

@@ -204,7 +204,22 @@ def test_routes_at_the_edges_of_their_rules():
     assert route(32, 256, 1, 32, 4096, 1, 256, 32000)[1:] == (64, 1, "parts", 1, 0)
     # 1024 parts over all rows, then one workgroup a row of the sampled select; r = 1024 is the split select's most
     assert route(64, 16, 0, 1, 65536, 64, 1024, 32000)[3:5] == ("parts", 16)
-    assert route(65, 16, 0, 1, 65536, 65, 1024, 32000)[3:5] == ("sampled", 4)
+    assert route(65, 16, 0, 1, 65536, 65, 1024, 32000).select == "one-workgroup"
+    assert route(65, 16, 0, 1, 65537, 65, 1024, 32000)[3:5] == ("wide", 4)
+    assert route(600, 16, 0, 1, 32768, 600, 1024, 32000)[3:5] == ("sampled", 1)
+    assert route(600, 16, 0, 1, 32769, 600, 1024, 32000).select == "one-workgroup"
+    # more than two parts a CU, no more rows than CUs, of at most 32768 keys: one workgroup a row
+    assert route(64, 16, 0, 1, 32768, 64, 1024, 64001).select == "parts"
+    assert route(65, 16, 0, 1, 32768, 65, 1024, 64001).select == "one-workgroup"
+    assert route(65, 16, 0, 1, 32768, 65, 1024, 1000).select == "groups"
+    assert route(256, 16, 0, 1, 12288, 256, 1024, 64001).select == "one-workgroup"
+    assert route(257, 16, 0, 1, 12288, 257, 1024, 64001).select == "parts"
+    # rows of one part and a large vocabulary: fixed lambda from 257 rows on, the rest past 1024
+    for rows, mode, V, want in ((256, "fixed", 32000, "parts"), (257, "fixed", 32000, "one-workgroup"),
+                                (257, "fixed", 16384, "parts"), (257, "nest", 32000, "parts"),
+                                (1025, "nest", 32000, "one-workgroup"), (1025, "fixed", 16384, "sampled")):
+        assert route(rows, 16, 0, 1, 4096, rows, 1000, V, mode=mode).select == want, (rows, mode, V)
+    assert route(1025, 16, 0, 1, 4097, 1025, 1000, 32000).select == "sampled"
     assert route(3, 16, 0, 1, 40000, 3, 1025).select == "sampled"
     assert route(3, 16, 0, 1, 40000, 3, 2049).select == "general"
     # 128-query batches on long rows: fused where the rows hold 2 r coarse tiles (1024 rows at d = 1024, 256 at
@@ -215,6 +230,7 @@ def test_routes_at_the_edges_of_their_rules():
     assert route(128, 128, 1, 1, 65800, 128, 64).select != "fused"
     # a workspace that holds no lists: one workgroup a row
     assert route(65, 16, 0, 1, 65536, 65, 1024, workspace_bytes=0).select == "one-workgroup"
+    assert route(3, 16, 0, 1, 40000, 3, 1025, 100, workspace_bytes=0).select == "general"
     assert route(17, 16, 0, 1, 65536, 17, 1024, workspace_bytes=0).select == "one-workgroup"
     assert route(16, 16, 0, 1, 65536, 16, 1024, workspace_bytes=0).select == "groups"
     assert route(3, 16, 0, 1, 40000, 3, 2048, workspace_bytes=0).select == "general"

@@ -8,6 +8,8 @@ import numpy as np
 import pytest
 import torch
 
+import select_paths
+
 pytestmark = pytest.mark.gpu
 
 knn = pytest.importorskip("paper_2405_19325_amd")
@@ -43,25 +45,36 @@ def _reference(dist, ko, qo, r, masked):
     return torch.stack(ids), torch.stack(ds)
 
 
-# queries and keys per set, d, dtype, r, V, largest entry of integer keys (0: normal keys)
+# queries and keys per set, d, dtype, r, V, largest entry of integer keys (0: normal keys), the selects of the
+# fixed-lambda step, of the masked step, and of both on the smallest workspace
 CASES = {
-    "split, 320 parts": (40, (8000, 5000, 4097, 7999), 64, torch.float32, 1000, 1000, 0),
-    "split, rows of one part": (45, (4096, 4000, 1024, 4500, 3001), 64, torch.float32, 1024, 1003, 0),
-    "split, every distance alike": (300, (4096,), 8, torch.float32, 64, 500, 1),
-    "groups, 5/4 r of them": (2, (5200, 7437), 16, torch.float32, 1024, 5001, 0),
-    "rows over 1024 parts": (1100, (3000, 4097), 8, torch.float32, 100, 37, 0),
-    "sampled, r over 1024": (3, (5000, 2100, 40000), 16, torch.float32, 2048, 40001, 0),
-    "sampled, long rows": (20, (262144,), 128, torch.bfloat16, 1024, 1003, 0),
-    "sampled from 16384": (18, (300000, 4099), 128, torch.float16, 1024, 1000, 0),
-    "sampled, few values": (18, (100000,), 128, torch.bfloat16, 900, 1001, 1),
-    "streamed, r over 2048": (2, (9000,), 32, torch.float32, 3000, 1000, 0),
+    "groups, 320 parts": (40, (8000, 5000, 4097, 7999), 64, torch.float32, 1000, 1000, 0, "groups", "groups", "one-workgroup"),
+    "split, 600 parts": (150, (8000, 5000), 64, torch.float32, 1000, 5001, 0, "parts", "parts", "one-workgroup"),
+    "split, rows of one part": (45, (4096, 4000, 1024, 4500, 3001), 64, torch.float32, 1024, 1003, 0, "parts", "parts",
+                                "one-workgroup"),
+    "split, every distance alike": (300, (4096,), 8, torch.float32, 64, 500, 1, "parts", "parts", "one-workgroup"),
+    "groups, 5/4 r of them": (2, (5200, 7437), 16, torch.float32, 1024, 5001, 0, "groups", "groups", "groups"),
+    "one workgroup a row, 900 parts": (90, (20000, 9000), 64, torch.float32, 1024, 5001, 0, "one-workgroup",
+                                       "one-workgroup", "one-workgroup"),
+    "one workgroup a row of one part": (300, (3000,), 8, torch.float32, 64, 17001, 0, "one-workgroup", "parts",
+                                        "one-workgroup"),
+    "one workgroup a short row": (1100, (3000,), 8, torch.float32, 64, 17001, 0, "one-workgroup", "one-workgroup",
+                                  "one-workgroup"),
+    "one workgroup a long row": (100, (48000, 33001), 16, torch.float32, 1000, 1000, 0, "one-workgroup", "one-workgroup",
+                                 "one-workgroup"),
+    "rows over 1024 parts": (1100, (3000, 4097), 8, torch.float32, 100, 37, 0, "sampled", "sampled", "one-workgroup"),
+    "sampled, r over 1024": (3, (5000, 2100, 40000), 16, torch.float32, 2048, 40001, 0, "sampled", "sampled", "general"),
+    "sampled, long rows": (20, (262144,), 128, torch.bfloat16, 1024, 1003, 0, "sampled", "sampled", "general"),
+    "sampled from 16384": (18, (300000, 4099), 128, torch.float16, 1024, 1000, 0, "sampled-16384", "sampled-16384", "general"),
+    "sampled, few values": (18, (100000,), 128, torch.bfloat16, 900, 1001, 1, "sampled", "sampled", "general"),
+    "streamed, r over 2048": (2, (9000,), 32, torch.float32, 3000, 1000, 0, "general", "general", "general"),
 }
 
 
 @pytest.mark.parametrize("share", [0.0, 0.02, 0.5], ids=["all-keys", "masked", "half-masked"])
 @pytest.mark.parametrize("name", list(CASES))
 def test_select_and_mixture(name, share):
-    q, sizes, d, dtype, r, V, top = CASES[name]
+    q, sizes, d, dtype, r, V, top, fixed, nest, small = CASES[name]
     masks = share > 0
     print(f"[gpu] select route: {name} masked={share}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(q + d + r)
@@ -94,6 +107,8 @@ def test_select_and_mixture(name, share):
     whole = prob.workspace
     for size in (whole.numel(), _smallest_workspace(prob)):
         prob.workspace = whole[:size]
+        want = small if size < whole.numel() else nest if masks else fixed
+        assert select_paths.of_problem(prob, "nest" if masks else "fixed").select == want
         if masks:  # lambda_t and the decoding outputs too
             out = prob.run_nest(0.3, 0.1, 0.5, key_mask=mask)
             lam = out["lambdas"].double()[:, None]
@@ -132,6 +147,7 @@ def test_one_workgroup_row_misjudged(case):
     p_lm = torch.full((B, V), 1.0 / V, device=dev)
     prob = knn.MixtureProblem(tq, tk, values, tko, tqo, p_lm, r, key_offsets_host=ko, query_offsets_host=qo)
     prob.workspace = prob.workspace[:_smallest_workspace(prob)]
+    assert select_paths.of_problem(prob).select == "one-workgroup"
     prob.run()
     ids, ds = _reference(knn.distances(tq, tk, tko, tqo), ko, qo, r, np.zeros(n, bool))
     assert torch.equal(prob.ids, ids) and torch.equal(prob.dists, ds)
