@@ -454,14 +454,22 @@ int multi_queries(int64_t d, knn_dtype dtype, int64_t max_queries) {
     return nq;
 }
 
+// Shares of the key rows: as many as leave at most a workgroup per CU over all
+// query groups (the registers leave room for one), in whole rows of 8, one an
+// XCD, each of which takes its workgroups apart from the others' -- but at
+// least one row.  With 88 shares of 3 groups an XCD had 33 workgroups for 32 CUs,
+// the last in a second pass: 4 x 7,000 keys of d = 256, 40 fp32 queries 73 us, 45 us with 80.
+int64_t multi_ranges(int64_t groups) {
+    const int64_t ranges = kMultiBlocks / (8 * groups) * 8;
+    return ranges < 8 ? 8 : ranges;
+}
+
 hipError_t launch_distances_multi(const DistPlan &plan, knn_dtype dtype, const DistArgs &args, int64_t S,
                                   hipStream_t stream) {
     const int64_t tiles = S * plan.tiles_per_set;
     if (tiles > 0x7fffffffLL || plan.groups < 1 || plan.groups > 65535 || args.rows_per_tile % kRows != 0)
         return hipErrorInvalidConfiguration;
-    // a workgroup per CU over all query groups, at least one 8-wide row of shares each
-    int64_t ranges = (kMultiBlocks / plan.groups + 7) / 8 * 8;
-    if (ranges < 8) ranges = 8;
+    const int64_t ranges = multi_ranges(plan.groups);
     const int64_t nblocks = ranges * plan.groups;
     const size_t lds = query_lds(args.d * elem_bytes(dtype), plan.nq);
     const dim3 grid(static_cast<unsigned>(nblocks));

@@ -1,4 +1,4 @@
-"""The row ranges of the matrix-core distance workgroups (csrc/tile_rows.h), compiled for the host: every row a
+"""Arithmetic of the distance launches, on the host.  The row ranges of the matrix-core distance workgroups (csrc/tile_rows.h), compiled for the host: every row a
 workgroup loads lies inside its set, and the passes of the fused select take every row once."""
 import ctypes
 import os
@@ -88,3 +88,14 @@ def test_sample_of_every_width(lib):
         rows, every = out
         assert rows % 256 == 0 and 256 <= rows <= rpt and every >= 1, (d, rpt, rows, every)
         assert 1 / 72 < rows / (rpt * every) < 1 / 48, (d, rpt, rows, every)
+
+
+def test_shares_of_several_queries_fit_every_xcd_at_once():
+    """The several-queries kernel runs one workgroup a CU, and the shares go to the 8 XCDs of 32 CUs in turn: those of
+    all query groups are at most 32 an XCD, and no fewer than leave less than one more share's room."""
+    shares = _lib.load()["_ZN5knnlm12multi_rangesEl"]
+    shares.argtypes, shares.restype = [ctypes.c_int64], ctypes.c_int64
+    for groups in range(1, 33):
+        assert shares(groups) % 8 == 0
+        assert 32 - groups < shares(groups) // 8 * groups <= 32
+    assert shares(4096) == 8
