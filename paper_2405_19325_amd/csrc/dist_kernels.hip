@@ -593,8 +593,9 @@ DistPlan plan_distances(int64_t d, knn_dtype dtype, int64_t S, int64_t max_keys,
         const int64_t passes = (mq + nq - 1) / nq;
         const int64_t rows = passes * (max_keys < 1 ? 1 : max_keys);  // that one set makes it read
         if ((passes > 1 || nq > 4) && S >= (kMultiMinRows + rows - 1) / rows) {
-            p.multi = true;
-            p.nq = multi_queries(d, dtype, mq);
+            const int many = multi_queries(d, dtype, mq);
+            p.multi = multi_pays(S, rows, d * elem_bytes(dtype), (mq + many - 1) / many);
+            if (p.multi) p.nq = many;
         }
     } else {
         p.cpl = 0;

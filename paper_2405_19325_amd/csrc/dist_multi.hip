@@ -464,6 +464,18 @@ int64_t multi_ranges(int64_t groups) {
     return ranges < 8 ? 8 : ranges;
 }
 
+// Each set past the shares costs every workgroup its place in the walk over
+// the sets (2 us for 64 of them) and one workgroup a barrier and the staging of
+// its queries: 25 to 35 ns a set and query group over the chip, where the streaming kernel finds its
+// set by one division.  That has to be a part of what the streaming kernel takes for the set,
+// about 0.3 ns and 0.1 ns a KiB for each row it reads.  Streaming kernel and this one, 4,096 sets:
+// 16 keys of d = 256, 8 queries, 38 and 137 us, 128 keys 216 and 241 us, 256 keys
+// 419 and 378 us; d = 1024, 12 queries (two passes), 16 keys 97 and 173 us, 64 keys 294 and
+// 237 us; d = 1000, 40 queries (5 passes, three groups here), 16 keys 248 and 504 us, 128 keys 1,413 and 1,046 us.
+bool multi_pays(int64_t S, int64_t rows, int64_t row_bytes, int64_t groups) {
+    return S <= multi_ranges(groups) || rows >= (600 * 1024 * groups + 3 * 1024 + row_bytes - 1) / (3 * 1024 + row_bytes);
+}
+
 hipError_t launch_distances_multi(const DistPlan &plan, knn_dtype dtype, const DistArgs &args, int64_t S,
                                   hipStream_t stream) {
     const int64_t tiles = S * plan.tiles_per_set;

@@ -109,6 +109,8 @@ constexpr int64_t kMultiBlocks = 256;
 constexpr int64_t kMultiMinRows = 10000;  // key rows x passes of the streaming kernel from which it is taken
 int multi_queries(int64_t d, knn_dtype dtype, int64_t max_queries);
 int64_t multi_ranges(int64_t groups);
+// rows: key rows that the streaming kernel would read for one set, over its passes
+bool multi_pays(int64_t S, int64_t rows, int64_t row_bytes, int64_t groups);
 hipError_t launch_distances_multi(const DistPlan &plan, knn_dtype dtype, const DistArgs &args, int64_t S,
                                   hipStream_t stream);
 // Bytes of the packed copy of n rows of d 16-bit elements: blocks of 16 rows

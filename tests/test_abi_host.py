@@ -228,6 +228,18 @@ def test_routes_at_the_edges_of_their_rules():
     assert route(128, 1024, 2, 1, 130048, 128, 64)[1::2] == (128, "wide", 0)
     assert route(128, 4096, 1, 1, 65800, 128, 64)[1::2] == (256, "fused", 0)
     assert route(128, 128, 1, 1, 65800, 128, 64).select != "fused"
+    # several queries a set: enough rows to read in all, and in each set where the sets outnumber the shares
+    def kernel(sets, keys, queries, d, dtype=1):
+        return route(sets * queries, d, dtype, sets, keys, queries, min(keys, 16)).kernel
+
+    assert [kernel(1, n, 8, 256) for n in (9999, 10000)] == ["streaming", "several-queries"]
+    assert [kernel(1, n, 8, 4096) for n in (2499, 2500)] == ["streaming", "several-queries"]  # four passes of two
+    assert [kernel(s, 100, 8, 256) for s in (256, 257)] == ["several-queries", "streaming"]
+    assert [kernel(4096, n, 8, 256) for n in (16, 171, 172)] == ["streaming", "streaming", "several-queries"]
+    assert [kernel(4096, n, 6, 256, 0) for n in (149, 150)] == ["streaming", "several-queries"]
+    assert [kernel(s, 64, 40, 1000) for s in (80, 81)] == ["several-queries", "streaming"]  # three query groups
+    assert kernel(4096, 128, 40, 1000) == "several-queries"
+    assert kernel(4096, 1000, 4, 256) == "streaming"  # one pass of four
     # a workspace that holds no lists: one workgroup a row
     assert route(65, 16, 0, 1, 65536, 65, 1024, workspace_bytes=0).select == "one-workgroup"
     assert route(3, 16, 0, 1, 40000, 3, 1025, 100, workspace_bytes=0).select == "general"

@@ -8,9 +8,13 @@ import numpy as np
 import pytest
 import torch
 
+import select_paths
+
 pytestmark = pytest.mark.gpu
 
 knn = pytest.importorskip("paper_2405_19325_amd")
+
+DTYPES = {torch.float32: 0, torch.bfloat16: 1, torch.float16: 2}
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -45,6 +49,7 @@ CASES = [
     ("8q-wide", (8, 6), (701, 660), 8192), ("9q", (9,), (3501,), 2048), ("15q", (15, 2), (4099, 31), 256),
     ("12q-two-groups", (12,), (910,), 8192),
     ("70 sets", tuple(1 + i % 6 for i in range(70)), tuple(1 + 7 * (i % 31) for i in range(70)), 768),
+    ("300 sets", tuple(i % 6 for i in range(300)), tuple(1 + 8 * (i % 51) for i in range(300)), 256),
     ("empty set", (2, 0, 2), (1700, 0, 1709), 5120), ("64q-segments", (64,), (40000,), 8),
 ]
 
@@ -56,6 +61,8 @@ def test_bits_of_one_query(name, rows, sizes, d, dtype, norms):
     if dtype == torch.float32:
         d = min(d, 4096)
     print(f"[gpu] multi {name} {dtype} norms={norms} d={d}", flush=True)
+    assert select_paths.route(sum(rows), d, DTYPES[dtype], len(sizes), max(sizes), max(rows), 1).kernel == \
+        "several-queries"
     q, k, ko, qo = _batch(rows, sizes, d, dtype, 7 + d)
     kn = knn.key_sqnorms(k) if norms else None
     got = knn.distances(q, k, _dev(ko), _dev(qo), key_sqnorms=kn, key_offsets_host=ko, query_offsets_host=qo)
