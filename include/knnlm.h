@@ -21,7 +21,9 @@
  * Memory.  Unless a parameter says "host", every pointer is a DEVICE pointer
  * (hipMalloc'd or torch CUDA storage) on the current device.  The caller owns
  * every buffer; the library allocates and frees nothing.  Scratch space comes
- * from the caller's `workspace`, sized by knn_lm_mixture_workspace_size().
+ * from the caller's `workspace`, of at least knn_lm_mixture_workspace_size()
+ * bytes; knn_lm_mixture_workspace_preferred() bytes let every call take its
+ * fastest kernels.
  *
  * Streams.  `stream` is a hipStream_t (NULL = the default stream).  Calls only
  * validate on the host and enqueue work; they never synchronise.  Outputs are
@@ -133,11 +135,11 @@ knn_status knn_lm_mixture(const void *queries, const void *keys, const float *ke
 /*
  * knn_lm_mixture_noalloc -- knn_lm_mixture without a workspace argument, for
  * callers that cannot allocate device memory (code under HIP graph capture,
- * serving loops that forbid allocation).  It computes exactly what
- * knn_lm_mixture computes, with the same kernels, and allocates nothing: its
- * scratch space is a static array of KNNLM_NOALLOC_SCRATCH_BYTES in device
- * memory, one per GPU, held from the library's first use on that GPU until
- * the process ends.  Its device address is looked up on the first call with
+ * serving loops that forbid allocation).  It is knn_lm_mixture on a workspace
+ * of KNNLM_NOALLOC_SCRATCH_BYTES (with the kernels that a workspace of that
+ * size gets, see knn_lm_mixture_workspace_preferred) and allocates nothing:
+ * its scratch space is a static array in device memory, one per GPU, held from
+ * the library's first use on that GPU until the process ends.  Its device address is looked up on the first call with
  * that GPU current (make that first call outside graph capture).
  *
  * Arguments as knn_lm_mixture; the caller still owns every input and output.
@@ -266,6 +268,23 @@ size_t knn_lm_mixture_workspace_size(int64_t B, int64_t d, int64_t V, int64_t S,
                                      int64_t total_keys, int64_t min_keys_per_set,
                                      int64_t max_keys_per_set, int64_t max_queries_per_set,
                                      knn_dtype dtype, int32_t r);
+
+/*
+ * Bytes of workspace with which a call of these sizes runs fastest (at least
+ * knn_lm_mixture_workspace_size(), 0 if they are invalid; the same for packed
+ * keys).  They hold the candidate lists of the selects that cut many, long or
+ * r > 1024 rows into parts, and the distances of finer tiles on small
+ * row-major stores; a call on a smaller workspace selects such rows by one
+ * workgroup each, over larger tiles.  Neighbours and distances are the same
+ * bits on either, p_m up to the order of float additions in the scatter.  The
+ * lists take at most 128 MiB or no more than the distances: 64 queries on sets
+ * of 65,536 keys of d = 4096 48.3 MiB (least 16.3), 20,000 on sets of 10,000 keys
+ * of d = 256 1.38 GiB (least 0.77).
+ */
+size_t knn_lm_mixture_workspace_preferred(int64_t B, int64_t d, int64_t V, int64_t S,
+                                          int64_t total_keys, int64_t min_keys_per_set,
+                                          int64_t max_keys_per_set, int64_t max_queries_per_set,
+                                          knn_dtype dtype, int32_t r);
 
 /*
  * knn_lm_mixture_validate -- the host-side argument checks of knn_lm_mixture,

@@ -20,7 +20,7 @@ from ._lib import DTYPES, KEYS_PACKED, PARTS, KnnError, load, status_string  # n
 
 __all__ = ["MixtureProblem", "mixture", "mixture_noalloc", "distances", "key_sqnorms", "pack_keys",
            "packed_keys_bytes", "mix", "mix_rrc", "spec_verify", "mask_words", "stream_read", "workspace_size",
-           "KnnError", "load", "status_string", "abi_version"]
+           "preferred_workspace_size", "KnnError", "load", "status_string", "abi_version"]
 
 _TORCH_DTYPES = {torch.float32: "f32", torch.bfloat16: "bf16", torch.float16: "f16"}
 
@@ -52,8 +52,15 @@ def abi_version() -> int:
 
 
 def workspace_size(B, d, V, S, total_keys, min_keys, max_keys, max_queries, dtype: str, r) -> int:
+    """Bytes of workspace that a call of these sizes needs."""
     return int(load().knn_lm_mixture_workspace_size(B, d, V, S, total_keys, min_keys, max_keys, max_queries,
                                                     DTYPES[dtype], r))
+
+
+def preferred_workspace_size(B, d, V, S, total_keys, min_keys, max_keys, max_queries, dtype: str, r) -> int:
+    """Bytes of workspace with which a call of these sizes runs fastest (what MixtureProblem allocates)."""
+    return int(load().knn_lm_mixture_workspace_preferred(B, d, V, S, total_keys, min_keys, max_keys, max_queries,
+                                                         DTYPES[dtype], r))
 
 
 class MixtureProblem:
@@ -111,11 +118,11 @@ class MixtureProblem:
         self.mu = float(1.0 / math.sqrt(self.d) if mu is None else mu)
         self.lam = float(lam)
         dev = queries.device
-        nbytes = load().knn_lm_mixture_workspace_size(self.B, self.d, self.V, self.S, self.total_keys,
-                                                      self.min_keys, self.max_keys, self.max_queries,
-                                                      self.dtype, self.r)
+        nbytes = load().knn_lm_mixture_workspace_preferred(self.B, self.d, self.V, self.S, self.total_keys,
+                                                           self.min_keys, self.max_keys, self.max_queries,
+                                                           self.dtype, self.r)
         if nbytes == 0:
-            _lib.check("knn_lm_mixture_workspace_size", self._validate(None, 0))
+            _lib.check("knn_lm_mixture_workspace_preferred", self._validate(None, 0))
         self.workspace = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=dev)
         self.p_m = torch.empty((self.B, self.V), dtype=torch.float32, device=dev)
         self.ids = torch.empty((self.B, self.r), dtype=torch.int32, device=dev)

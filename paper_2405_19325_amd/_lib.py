@@ -39,6 +39,7 @@ SIGNATURES: Dict[str, tuple] = {
                           P, P, P, P, P, P, P, P, P, P, SZ, P]),
     "knn_spec_verify": (I, [P, P, P, P, I64, F, P, P, P, P]),
     "knn_lm_mixture_workspace_size": (SZ, [I64, I64, I64, I64, I64, I64, I64, I64, I, I32]),
+    "knn_lm_mixture_workspace_preferred": (SZ, [I64, I64, I64, I64, I64, I64, I64, I64, I, I32]),
     "knn_lm_mixture_validate": (I, [P, P, P, P, P, P, I64, I64, I64, I64, I64, I64, I64, I64, I, I32, F, F,
                                     P, P, P, P, SZ]),
     "knn_distances": (I, [P, P, P, P, P, I64, I64, I64, I64, I64, I, P, I64, P]),

@@ -569,10 +569,21 @@ size_t knn_lm_mixture_workspace_size(int64_t B, int64_t d, int64_t V, int64_t S,
     if (check_sizes(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, r,
                     true) != KNN_OK)
         return 0;
+    return least_workspace(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, r);
+}
+
+size_t knn_lm_mixture_workspace_preferred(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total_keys,
+                                          int64_t min_keys_per_set, int64_t max_keys_per_set,
+                                          int64_t max_queries_per_set, knn_dtype dtype, int32_t r) {
+    const knn_dtype et = base_dtype(dtype);
+    const size_t least = knn_lm_mixture_workspace_size(B, d, V, S, total_keys, min_keys_per_set, max_keys_per_set,
+                                                       max_queries_per_set, et, r);
+    if (least == 0) return 0;
     // one size for the call on packed and on row-major keys
     const size_t row_major = layout(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, false, r, SIZE_MAX).total;
     const size_t packed = layout(B, d, S, min_keys_per_set, max_keys_per_set, max_queries_per_set, et, true, r, SIZE_MAX).total;
-    return row_major > packed ? row_major : packed;
+    const size_t most = row_major > packed ? row_major : packed;
+    return most > least ? most : least;
 }
 
 knn_status knn_lm_mixture_validate(const void *queries, const void *keys, const int32_t *values,

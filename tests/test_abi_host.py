@@ -3,6 +3,7 @@ function include/knnlm.h declares, and rejects bad arguments before enqueuing
 anything."""
 import ctypes
 import os
+import random
 
 import pytest
 
@@ -248,13 +249,44 @@ def test_routes_at_the_edges_of_their_rules():
     assert route(3, 16, 0, 1, 40000, 3, 2048, workspace_bytes=0).select == "general"
 
 
-def test_least_workspace_is_that_of_whole_tiles(lib):
-    """A query batch on a small row-major store takes finer tiles than the 4096 rows that it needs the workspace of."""
-    sizes = dict(B=128, d=256, V=32000, S=62, total_keys=16404, min_keys=3, max_keys=549, max_queries=18, dtype=1, r=3)
-    rows_and_lists = 128 * (4 * 4096 + 8 * 4096)
-    assert _ws_size(lib, dict(BASE, **sizes)) > rows_and_lists
-    assert _validate(lib, ws_bytes=_ws_size(lib, dict(BASE, **sizes)), **sizes) == OK
-    assert _validate(lib, ws_bytes=rows_and_lists, **sizes) == WORKSPACE
+def _preferred(lib, a):
+    return lib.knn_lm_mixture_workspace_preferred(a["B"], a["d"], a["V"], a["S"], a["total_keys"], a["min_keys"],
+                                                  a["max_keys"], a["max_queries"], a["dtype"], a["r"])
+
+
+def test_workspace_size_is_the_least_accepted(lib):
+    """A workspace of knn_lm_mixture_workspace_size() is accepted and a byte less refused, of query batches on small
+    row-major stores (whose finer tiles need less) and of rows whose larger selects want more, too."""
+    rng = random.Random(5)
+    for _ in range(2000):
+        S = rng.choice([1, 2, 8, 60, 1000])
+        keys = int(2 ** rng.uniform(3, 18))
+        q = int(2 ** rng.uniform(0, 8))
+        d = rng.choice([8, 128, 384, 1000, 1024, 4096, 8192])
+        few = max(1, int(keys * rng.uniform(0.3, 1)))
+        a = dict(BASE, B=S * q, d=d, S=S, total_keys=S * keys, min_keys=few, max_keys=keys, max_queries=q,
+                 dtype=rng.choice([0, 1, 2]), r=rng.choice([1, 64, 1000, 1024, 2048, 4096]))
+        a["r"] = min(a["r"], few)
+        size, most = _ws_size(lib, a), _preferred(lib, a)
+        assert 0 < size <= most, a
+        kw = {k: a[k] for k in a if k not in ("mu", "lam")}
+        assert _validate(lib, ws_bytes=size, **kw) == OK and _validate(lib, ws_bytes=most, **kw) == OK, a
+        assert _validate(lib, ws_bytes=size - 1, **kw) == WORKSPACE, a
+        if a["dtype"] != 0:
+            assert _preferred(lib, dict(a, dtype=a["dtype"] | KEYS_PACKED)) == most, a
+
+
+def test_workspace_sizes_of_the_header_examples(lib):
+    """The static scratch array serves what the header says, by the size that it gates on."""
+    scratch = 32 << 20
+    long_rows = dict(BASE, B=64, S=64, total_keys=64 * 65536)
+    assert 16 << 20 < _ws_size(lib, long_rows) < 17 << 20
+    assert 48 << 20 < _preferred(lib, long_rows) < 49 << 20
+    wide = dict(BASE, B=16, d=8192, S=16, total_keys=16 * 131072, min_keys=131072, max_keys=131072)
+    assert _ws_size(lib, wide) <= scratch
+    many = dict(BASE, B=20000, d=256, S=2000, total_keys=2000 * 10000, min_keys=10000, max_keys=10000, max_queries=10)
+    assert 760 << 20 < _ws_size(lib, many) < 790 << 20 and 1400 << 20 < _preferred(lib, many) < 1415 << 20
+    assert _preferred(lib, dict(BASE, r=0)) == 0
 
 
 @pytest.mark.parametrize("rows,keys,r", [(100_000, 1000, 64), (100_000, 4096, 1024), (10_000, 1000, 1000), (4096, 1000, 64)])
@@ -262,7 +294,7 @@ def test_lists_of_many_short_rows_are_bounded(lib, rows, keys, r):
     """A select's candidate lists take at most 128 MiB, or no more than the distances, the group minima and
     extrema a tenth of those."""
     S = rows // 10
-    size = _ws_size(lib, dict(BASE, B=rows, d=256, S=S, total_keys=keys * S, min_keys=keys, max_keys=keys,
+    size = _preferred(lib, dict(BASE, B=rows, d=256, S=S, total_keys=keys * S, min_keys=keys, max_keys=keys,
                               max_queries=10, r=r))
     dist = 4 * rows * (keys + 256)  # the row rounded up to its tiles of at most 256
     assert dist * keys // (keys + 256) < size < 1.2 * dist + max(dist, 129 << 20)

@@ -83,7 +83,9 @@ def test_bits_of_the_packed_kernel_in_256_row_passes(q, S, n, d, norms):
 
 def test_workspace_of_both_key_layouts():
     """One workspace size serves a batch on row-major and on packed keys, finer tiles or not."""
+    lib = knn.load()
     for q, n in ((16, 3001), (40, 8193), (130, 33000), (16, 262144)):
-        a, b = (knn.load().knn_lm_mixture_workspace_size(q, 1024, 500, 1, n, n, n, q, dt, 64)
-                for dt in (knn.DTYPES["bf16"], knn.DTYPES["bf16"] | knn.KEYS_PACKED))
-        assert a == b > 0
+        for size in (lib.knn_lm_mixture_workspace_size, lib.knn_lm_mixture_workspace_preferred):
+            a, b = (size(q, 1024, 500, 1, n, n, n, q, dt, 64)
+                    for dt in (knn.DTYPES["bf16"], knn.DTYPES["bf16"] | knn.KEYS_PACKED))
+            assert a == b > 0

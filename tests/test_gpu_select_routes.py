@@ -25,12 +25,11 @@ def _device():
 
 
 def _smallest_workspace(prob):
-    """The fewest bytes (a multiple of 256) that knn_lm_mixture accepts for the problem."""
-    lo, hi = 0, prob.workspace.numel() // 256
-    while hi - lo > 1:
-        mid = (lo + hi) // 2
-        lo, hi = (lo, mid) if prob._validate(256, mid * 256) == 0 else (mid, hi)
-    return hi * 256
+    """The fewest bytes that knn_lm_mixture accepts for the problem."""
+    size = knn.load().knn_lm_mixture_workspace_size(prob.B, prob.d, prob.V, prob.S, prob.total_keys, prob.min_keys,
+                                                    prob.max_keys, prob.max_queries, prob.dtype, prob.r)
+    assert prob._validate(256, size) == 0 and prob._validate(256, size - 1) != 0
+    return size
 
 
 def _reference(dist, ko, qo, r, masked):
