@@ -248,8 +248,14 @@ knn_status knn_spec_verify(const float *p_max, const float *p_draft, const int32
  * KNN_PART_DISTANCES followed by either KNN_PART_SELECT_MIX or KNN_PART_SELECT
  * then KNN_PART_MIX, on one stream with one workspace, computes what
  * knn_lm_mixture computes (neighbours and distances bit for bit; p_m up to
- * the order of float additions in the scatter).  Pointers a stage does not
- * use may be NULL (DISTANCES: values, p_lm, p_m, nbr_ids, nbr_dists; SELECT:
+ * the order of float additions in the scatter).  The select stages may run
+ * more than once after one DISTANCES.  The stages take the same sizes and
+ * hints, but not necessarily the same workspace_bytes (each at least
+ * knn_lm_mixture_workspace_size()) nor, past DISTANCES, the packed flag: what
+ * passes between them lies as in the least workspace.  So a stage can be
+ * slower than within the whole call (larger tiles on small row-major stores,
+ * a parts kernel where the whole call reads group minima).
+ * Pointers a stage does not use may be NULL (DISTANCES: values, p_lm, p_m, nbr_ids, nbr_dists; SELECT:
  * queries, keys, key_sqnorms, values, p_lm, p_m; MIX: queries, keys,
  * key_sqnorms, workspace; SELECT_MIX: queries, keys, key_sqnorms).
  */

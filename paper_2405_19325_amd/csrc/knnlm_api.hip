@@ -57,7 +57,7 @@ bool fused_shape(int64_t B, int64_t d, knn_dtype dtype, int64_t max_queries, int
 }
 
 Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64_t max_queries, knn_dtype dtype,
-                 int32_t r, int rows_per_tile, bool roomy, bool may_fuse = true) {
+                 int32_t r, int rows_per_tile, bool roomy, bool may_fuse = true, bool stage = false) {
     Layout L{};
     L.rows_per_tile = rows_per_tile;
     L.tiles_per_set = (max_keys + L.rows_per_tile - 1) / L.rows_per_tile;
@@ -89,6 +89,11 @@ Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64
     bool many = false;
     if (L.path == kSplitSelect)
         L.group_rows = select_group_rows(L.ld, min_keys, r, L.rows_per_tile, !mfma_shape(d, dtype, max_queries), many);
+    // a stage on its own: only the minima that every workspace has, in their own place
+    if (stage && (!many || B * L.split_parts > kSplitFewBlocks)) {
+        L.group_rows = 0;
+        many = false;
+    }
     L.off_gmin = align_up(L.off_fallback + (L.fused ? sizeof(uint32_t) : 0));
     const size_t gmin_words = many ? static_cast<size_t>(B) * static_cast<size_t>(4 * L.tiles_per_set) : 0;
     L.total = align_up(L.off_gmin + sizeof(float) * gmin_words);
@@ -106,13 +111,18 @@ Layout layout_of(int64_t B, int64_t d, int64_t min_keys, int64_t max_keys, int64
 // rows: its sample has too few pieces there (128 queries on 70,000 keys of d =
 // 1024, r = 64, a step: 190 us fused over 256-row tiles, 81 us by the wide select
 // over 128-row ones; 156 us over the coarse ones).
+// A stage on its own (knn_lm_mixture_part) takes the coarse tiles and, of the
+// group minima, those of the least workspace: what it leaves for another stage
+// lies where the sizes alone say, whatever the other is told of the workspace's
+// size, the key layout (which a select has no use for) or the shortest row, and
+// stays there when a select runs twice.
 Layout layout(int64_t B, int64_t d, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries, knn_dtype dtype,
-              bool packed, int32_t r, size_t bytes) {
+              bool packed, int32_t r, size_t bytes, bool stage = false) {
     const int rows = dist_tile_rows(d, dtype, S, max_keys, max_queries);
-    Layout L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, true);
-    if (!packed && !L.fused && mfma_shape(d, dtype, max_queries))
+    Layout L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, true, true, stage);
+    if (!stage && !packed && !L.fused && mfma_shape(d, dtype, max_queries))
         L = layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, mfma_fine_rows(rows, S, max_keys, max_queries), true, false);
-    return L.total <= bytes ? L : layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, false);
+    return L.total <= bytes ? L : layout_of(B, d, min_keys, max_keys, max_queries, dtype, r, rows, false, true, stage);
 }
 
 // The least workspace that a call is accepted with: the small layout on the
@@ -289,8 +299,10 @@ FusedArgs fused_args(const Layout &L, char *ws) {
     return f;
 }
 
-knn_status run_part(const Call &c, int part, hipStream_t stream) {
-    const Layout L = layout(c.B, c.d, c.S, c.min_keys, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes);
+// One stage, of a whole call or (stage) run on its own.
+knn_status run_part(const Call &c, int part, hipStream_t stream, bool stage = false) {
+    const Layout L = layout(c.B, c.d, c.S, c.min_keys, c.max_keys, c.max_queries, c.dtype, c.packed, c.r, c.workspace_bytes,
+                            stage);
     char *ws = static_cast<char *>(c.workspace);
     float *dist = ws ? reinterpret_cast<float *>(ws + L.off_dist) : nullptr;
     float *tmin = ws ? reinterpret_cast<float *>(ws + L.off_tmin) : nullptr;
@@ -559,7 +571,7 @@ knn_status knn_lm_mixture_part(knn_part part, const void *queries, const void *k
                              lambda, p_m, nbr_ids, nbr_dists, workspace, workspace_bytes);
     const knn_status st = validate_part(c, part);
     if (st != KNN_OK) return st;
-    return run_part(c, part, static_cast<hipStream_t>(stream));
+    return run_part(c, part, static_cast<hipStream_t>(stream), true);
 }
 
 size_t knn_lm_mixture_workspace_size(int64_t B, int64_t d, int64_t V, int64_t S, int64_t total_keys,
@@ -733,12 +745,12 @@ int knn_abi_version(void) { return KNNLM_ABI_VERSION; }
  * bytes), its rows per tile, its queries per workgroup, the select
  * (SelectRoute::Kind) with a mixture of `mode` (MixMode) over V tokens, its
  * parts per row, rows per key group (0: no group minima), and whether the
- * fused select runs. */
+ * fused select runs; of a whole call or of its stages one at a time. */
 void knnlm_route(int64_t B, int64_t d, int64_t V, int64_t S, int64_t min_keys, int64_t max_keys, int64_t max_queries,
-                 knn_dtype dtype, int32_t r, int mode, size_t workspace_bytes, int32_t *out) {
+                 knn_dtype dtype, int32_t r, int mode, size_t workspace_bytes, int stage, int32_t *out) {
     const knn_dtype et = base_dtype(dtype);
     const bool packed = packed_flag(dtype);
-    const Layout L = layout(B, d, S, min_keys, max_keys, max_queries, et, packed, r, workspace_bytes);
+    const Layout L = layout(B, d, S, min_keys, max_keys, max_queries, et, packed, r, workspace_bytes, stage != 0);
     const DistPlan p = plan_distances(d, et, S, max_keys, max_queries, nullptr, nullptr);
     SelectArgs a{};
     a.path = L.path;

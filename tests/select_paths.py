@@ -22,22 +22,24 @@ class Route(NamedTuple):
 
 
 def route(B: int, d: int, dtype: int, S: int, max_keys: int, max_queries: int, r: int, V: Optional[int] = None,
-          min_keys: Optional[int] = None, mode: str = "fixed", workspace_bytes: int = ANY_BYTES) -> Route:
-    """Of a whole call with a mixture of `mode` over V tokens (V None: no mixture).  select is "fused", "groups" or
+          min_keys: Optional[int] = None, mode: str = "fixed", workspace_bytes: int = ANY_BYTES,
+          stage: bool = False) -> Route:
+    """Of a whole call (stage: of knn_lm_mixture_part's stages) with a mixture of `mode` over V tokens (V None: no mixture).  select is "fused", "groups" or
     "parts" (the split select, from group minima or from the parts kernel's sample), "wide", "sampled" or
     "sampled-16384", "one-workgroup" (the row in registers) or "general" (streamed)."""
     f = _lib.load()["knnlm_route"]
     f.restype = None
-    f.argtypes = [ctypes.c_int64] * 7 + [ctypes.c_int, ctypes.c_int32, ctypes.c_int, ctypes.c_size_t, ctypes.c_void_p]
+    f.argtypes = [ctypes.c_int64] * 7 + [ctypes.c_int, ctypes.c_int32, ctypes.c_int, ctypes.c_size_t, ctypes.c_int,
+                                        ctypes.c_void_p]
     out = (ctypes.c_int32 * 7)()
     f(B, d, V or 0, S, max_keys if min_keys is None else min_keys, max_keys, max_queries, dtype, r,
-      MODES[mode] if V else 0, workspace_bytes, out)
+      MODES[mode] if V else 0, workspace_bytes, int(stage), out)
     kernel, tile, queries, select, parts, group, fused = out
     return Route(KERNELS[kernel], tile, queries, "fused" if fused else SELECTS[select], parts, group)
 
 
-def of_problem(prob, mode: str = "fixed", workspace_bytes: Optional[int] = None) -> Route:
+def of_problem(prob, mode: str = "fixed", workspace_bytes: Optional[int] = None, stage: bool = False) -> Route:
     """Of a MixtureProblem's calls (mode "none": the select alone)."""
     return route(prob.B, prob.d, prob.dtype, prob.S, prob.max_keys, prob.max_queries, prob.r,
                  None if mode == "none" else prob.V, prob.min_keys, mode,
-                 prob.workspace.numel() if workspace_bytes is None else workspace_bytes)
+                 prob.workspace.numel() if workspace_bytes is None else workspace_bytes, stage)

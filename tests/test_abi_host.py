@@ -289,6 +289,29 @@ def test_workspace_sizes_of_the_header_examples(lib):
     assert _preferred(lib, dict(BASE, r=0)) == 0
 
 
+def test_stages_agree_on_what_lies_between_them():
+    """What one stage leaves for another does not depend on the workspace's size, on the key layout or on the
+    shortest row."""
+    from select_paths import route
+
+    rng = random.Random(6)
+    seen = set()
+    for _ in range(3000):
+        S, q, d = rng.choice([1, 2, 8, 60, 1000]), int(2 ** rng.uniform(0, 8)), rng.choice([16, 128, 1000, 1024, 4096])
+        keys, dtype = int(2 ** rng.uniform(5, 18)), rng.choice([0, 1, 2])
+        r = min(rng.choice([16, 64, 1000, 1024, 2048]), keys)
+        args = (S * q, d, dtype, S, keys, q, r, rng.choice([None, 1000, 32000]))
+        one = route(*args, stage=True)
+        others = [route(*args, stage=True, workspace_bytes=0), route(*args, min_keys=r, stage=True)]
+        if one.kernel == "matrix-core":
+            others.append(route(*args[:2], dtype | KEYS_PACKED, *args[3:], stage=True))
+        for o in others:
+            assert (o.tile_rows, o.group_rows, o.select == "fused") == (one.tile_rows, one.group_rows,
+                                                                       one.select == "fused"), args
+        seen.add((one.tile_rows == route(*args).tile_rows, one.group_rows == route(*args).group_rows))
+    assert seen >= {(True, True), (False, True), (True, False)}  # whole calls differ in either
+
+
 @pytest.mark.parametrize("rows,keys,r", [(100_000, 1000, 64), (100_000, 4096, 1024), (10_000, 1000, 1000), (4096, 1000, 64)])
 def test_lists_of_many_short_rows_are_bounded(lib, rows, keys, r):
     """A select's candidate lists take at most 128 MiB, or no more than the distances, the group minima and
