@@ -100,8 +100,8 @@ __device__ __forceinline__ float query_lambda(const MixArgs &m, int64_t b, float
 
 // The rank among M keys sampled from a row of N that aims at about r + 4
 // standard deviations + 4 samples' worth of its keys.
-__device__ __host__ inline uint32_t sample_rank(uint32_t r, int M, float N) {
-    const float k0 = ceilf(static_cast<float>(r) * static_cast<float>(M) / N);
+__device__ __host__ inline uint32_t sample_rank(uint32_t r, float M, float N) {
+    const float k0 = ceilf(static_cast<float>(r) * M / N);
     return static_cast<uint32_t>(k0 + ceilf(4.0f * sqrtf(k0)) + 4.0f);
 }
 
@@ -562,11 +562,6 @@ __device__ __forceinline__ void consume_loads(const float4 (&pre)[NV4]) {
     asm volatile("" ::"v"(t));
 }
 
-// p_M row b with weight lam of p_LM: weights wj (unnormalised softmax terms, sum z) are scatter-added
-// onto their tokens tok (-1: none) one vocabulary tile of TILE entries at a
-// time in LDS; each tile's p_LM slice sits in registers (prefetched by the
-// caller for the first tile when `first` is given) and is mixed with 16-byte
-// accesses.
 // The largest value over the block and the lowest index holding it (every
 // thread gets both): v >= 0 or -1 for "none"; red holds 2 * kNumWaves words
 // and is free again on return.
@@ -601,11 +596,6 @@ __device__ __forceinline__ void note_entry(float v, int32_t w, int32_t dtok, flo
     }
 }
 
-// p_M row b with weight lam of p_LM: weights wj (unnormalised softmax terms, sum z) are scatter-added
-// onto their tokens tok (-1: none) one vocabulary tile of TILE entries at a
-// time in LDS; each tile's p_LM slice sits in registers (prefetched by the
-// caller for the first tile when `first` is given) and is mixed with 16-byte
-// accesses.
 // 64-bit max / min over the block (every thread gets the result); red holds
 // kNumWaves entries and is free again on return.
 __device__ __forceinline__ uint64_t block_max_u64(uint64_t v, uint64_t *red) {
@@ -948,8 +938,7 @@ __global__ __launch_bounds__(kT) void k_select_fast(SelectArgs a, MixArgs m) {
         // Sample rank aiming at about r + 4 sd + 4 samples' worth of keys: the
         // count of keys below the threshold then lies in [r, kFastCap] with
         // overwhelming probability; otherwise the general path runs.
-        const float k0f = ceilf(static_cast<float>(r_eff) * static_cast<float>(ns) / static_cast<float>(N));
-        const uint32_t ks = static_cast<uint32_t>(k0f + ceilf(4.0f * sqrtf(k0f)) + 4.0f);
+        const uint32_t ks = sample_rank(r_eff, static_cast<float>(ns), static_cast<float>(N));
         if (ks < ns) {
             if (tid == 0) { sh.lo = bmin; sh.hi = bmax + 1u; sh.below = 0u; sh.cnt = ns; }
             __syncthreads();
@@ -1109,8 +1098,7 @@ __global__ __launch_bounds__(kT) void k_select_parts(SelectArgs a, MixArgs m, in
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (sb[u] - smin < w) atomicAdd(&hist[(sb[u] - smin) >> shift], 1u);
-        const float k0f = ceilf(static_cast<float>(r_eff) * static_cast<float>(kSplitSamples) / static_cast<float>(N));
-        const uint32_t ks = static_cast<uint32_t>(k0f + ceilf(4.0f * sqrtf(k0f)) + 4.0f);
+        const uint32_t ks = sample_rank(r_eff, static_cast<float>(kSplitSamples), static_cast<float>(N));
         __syncthreads();
         if (tid < kWave) {
             // the end of the bin holding the ks-th sample: at least ks samples lie below it
@@ -1765,7 +1753,7 @@ __global__ __launch_bounds__(kT) void k_select_wide_parts(SelectArgs a, int part
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (lane_word(sv[u], e) - lo < w) atomicAdd(&hist[(lane_word(sv[u], e) - lo) >> shift], 1u);
-            const uint32_t ks = sample_rank(r_eff, kSamples, static_cast<float>(N));
+            const uint32_t ks = sample_rank(r_eff, static_cast<float>(kSamples), static_cast<float>(N));
             __syncthreads();
             if (tid < kWave) {
                 const uint32_t j = ks < static_cast<uint32_t>(kSamples) ? wave_pick_bin(hist, ks, lane) : ~0u;
@@ -2026,8 +2014,7 @@ __global__ __launch_bounds__(kT) void k_fused_threshold(SelectArgs a, FusedArgs 
         lo = v < kMaskedBits ? min(lo, v) : lo;
         if (p < kT) pmin[p] = v;  // an all-masked piece reads as 0xffffffff
     }
-    const float k0f = ceilf(static_cast<float>(r_eff) * static_cast<float>(M) / static_cast<float>(N > 0 ? N : 1));
-    const uint32_t ks = static_cast<uint32_t>(k0f + ceilf(4.0f * sqrtf(k0f)) + 4.0f);
+    const uint32_t ks = sample_rank(r_eff, static_cast<float>(M), static_cast<float>(N > 0 ? N : 1));
     __syncthreads();
     // the end of the range: the ks-th smallest piece minimum (rank by comparison), else +infinity
     uint32_t hb = kMaskedBits;
@@ -2328,7 +2315,7 @@ int select_sampled_parts(int64_t B, int64_t ld, int r, SelectPath &path) {
     if (select_in_registers(ld, r) && ld > kRegisterKeys) return 0;
     for (int u = 1; u <= 4; u += 3) {
         const int M = 4 * kT * u;
-        const float ks = static_cast<float>(sample_rank(static_cast<uint32_t>(r), M, static_cast<float>(ld)));
+        const float ks = static_cast<float>(sample_rank(static_cast<uint32_t>(r), static_cast<float>(M), static_cast<float>(ld)));
         const float keys = ks * static_cast<float>(ld) / static_cast<float>(M);  // kept of a row, on average
         if (ld > kWideCap && keys + 4.0f * keys / sqrtf(ks) > static_cast<float>(kWideCap)) continue;
         const int parts = wide_parts(B, ld, kSampledBlocks);

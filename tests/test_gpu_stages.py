@@ -69,3 +69,14 @@ def test_stages_of_unlike_workspaces(name):
                 assert torch.equal(prob.ids, ids) and torch.equal(prob.dists, dists), (first, size, part)
                 if part == "select_mix":
                     torch.testing.assert_close(prob.p_m, p_m, rtol=1e-5, atol=1e-8)
+
+
+@pytest.mark.parametrize("public", [False, True], ids=["handle", "public name"])
+def test_current_stream(public, monkeypatch):
+    if public:
+        monkeypatch.setattr(knn, "_raw_stream", None)
+    side = torch.cuda.Stream()
+    assert knn._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert knn._stream() == side.cuda_stream
+    assert knn._stream(side) == side.cuda_stream
