@@ -43,3 +43,14 @@ def of_problem(prob, mode: str = "fixed", workspace_bytes: Optional[int] = None,
     return route(prob.B, prob.d, prob.dtype, prob.S, prob.max_keys, prob.max_queries, prob.r,
                  None if mode == "none" else prob.V, prob.min_keys, mode,
                  prob.workspace.numel() if workspace_bytes is None else workspace_bytes, stage)
+
+
+def take(prob, select: str, *modes: str):
+    """Has prob's calls (steps of these modes, by default of a fixed lambda) take the select `select`: on its own
+    workspace or, where they take another there, on the smallest accepted one."""
+    modes = modes or ("fixed",)
+    if any(of_problem(prob, m).select != select for m in modes):
+        prob.workspace = prob.workspace[:_lib.load().knn_lm_mixture_workspace_size(
+            prob.B, prob.d, prob.V, prob.S, prob.total_keys, prob.min_keys, prob.max_keys, prob.max_queries, prob.dtype,
+            prob.r)]
+    assert {of_problem(prob, m).select for m in modes} == {select}, [of_problem(prob, m) for m in modes]

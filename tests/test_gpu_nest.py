@@ -15,6 +15,7 @@ import torch
 
 import oracle
 import parity
+import select_paths
 from oracle import nest
 from workloads import gen
 
@@ -82,14 +83,12 @@ def _check_decisions(out, vals, ko, qo, draft=None):
     return want
 
 
-# (path, n keys per set, queries, r, d): the split select needs B * ceil(n / 4096)
-# <= 256, the one-workgroup select n <= 65536 and r <= 1024, the wide one rows of
-# more than 65536 keys in at least 2 r distance tiles with r <= 2048, the general
-# one the rest; 16 or more bf16 queries of a set with d % 128 == 0 take the matrix cores.
-PATHS = [("split", 40000, 6, 1024, 4), ("one-workgroup", 40000, 40, 1024, 4),
-         ("wide-long-row", 70000, 6, 1024, 4), ("general-long-row", 70000, 6, 2500, 4),
-         ("general-r2048", 40000, 3, 2048, 4),
-         ("matrix-core", 20000, 32, 1024, 128)]
+# (name, select, n keys per set, queries, r, d); one-workgroup and, at r = 2048, general run on the smallest
+# workspace; 16 or more bf16 queries of a set with d % 128 == 0 take the matrix cores.
+PATHS = [("split", "groups", 40000, 6, 1024, 4), ("split-400-parts", "groups", 40000, 40, 1024, 4),
+         ("one-workgroup", "one-workgroup", 40000, 40, 1024, 4), ("wide-long-row", "wide", 70000, 6, 1024, 4),
+         ("general-long-row", "general", 70000, 6, 2500, 4), ("general-r2048", "general", 40000, 3, 2048, 4),
+         ("sampled-r2048", "sampled", 40000, 3, 2048, 4), ("matrix-core", "parts", 20000, 32, 1024, 128)]
 
 
 # The matrix cores serve 16-bit keys only, so that path runs in bf16 alone.
@@ -97,9 +96,9 @@ MASKED_CASES = [(p, dt) for p in PATHS for dt in (torch.float32, torch.bfloat16)
                 if not (p[0] == "matrix-core" and dt == torch.float32)]
 
 
-@pytest.mark.parametrize("path,n,B,r,d,dtype", [(*p, dt) for p, dt in MASKED_CASES],
+@pytest.mark.parametrize("path,select,n,B,r,d,dtype", [(*p, dt) for p, dt in MASKED_CASES],
                          ids=[f"{p[0]}-{str(dt).split('.')[-1]}" for p, dt in MASKED_CASES])
-def test_masked_exact_integer_inputs(path, n, B, r, d, dtype):
+def test_masked_exact_integer_inputs(path, select, n, B, r, d, dtype):
     _say(f"masked exact integers: {path} n={n} B={B} r={r} d={d} {dtype}")
     rng, q, k, vals, p_lm = _integer_store(n, B, d, 60 + r + d)
     masked = rng.choice(n, n // 3, replace=False)
@@ -107,6 +106,7 @@ def test_masked_exact_integer_inputs(path, n, B, r, d, dtype):
     masked = np.union1d(masked, np.flatnonzero(np.all(k[:, :3] == 0, axis=1))[:5])
     ko, qo = np.array([0, n]), np.array([0, B])
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, dtype)
+    select_paths.take(prob, select, "nest")
     out = prob.run_nest(ALPHA, TAU, DELTA, key_mask=knn.mask_words(masked, n, "cuda"))
     torch.cuda.synchronize()
     o_ids, o_d = oracle.select(q, k, "f32", ko, qo, r, key_mask=_bits(masked, n))
@@ -121,18 +121,20 @@ def test_masked_exact_integer_inputs(path, n, B, r, d, dtype):
     _check_decisions(out, vals, ko, qo)
 
 
-@pytest.mark.parametrize("path,B,r", [("split", 2, 64), ("one-workgroup", 300, 64), ("general", 2, 2048)])
+@pytest.mark.parametrize("path,B,r", [("groups", 2, 64), ("parts", 300, 64), ("one-workgroup", 300, 64),
+                                      ("sampled", 2, 2048), ("general", 2, 2048)])
 def test_fewer_unmasked_keys_than_r(path, B, r):
     """Set 0 keeps r/2 unmasked keys, set 1 none: pi ends in absent slots (id -1,
     distance +inf) that carry no weight, and a query with no neighbour gets
     p_M = lambda_t p_LM with lambda_t = sigmoid((1 - alpha) / tau)."""
     _say(f"fewer unmasked keys than r: {path}")
-    n = 3000 if path != "general" else 5000
+    n = 3000 if r == 64 else 5000
     rng, q, k, vals, p_lm = _integer_store(2 * n, 2 * B, 4, 70 + B)
     ko, qo = np.array([0, n, 2 * n]), np.array([0, B, 2 * B])
     keep = rng.choice(n, r // 2, replace=False)
     masked = np.concatenate([np.setdiff1d(np.arange(n), keep), np.arange(n, 2 * n)])
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, torch.float32)
+    select_paths.take(prob, path, "nest")
     out = prob.run_nest(ALPHA, TAU, DELTA, key_mask=knn.mask_words(masked, 2 * n, "cuda"))
     torch.cuda.synchronize()
     o_ids, o_d = oracle.select(q, k, "f32", ko, qo, r, key_mask=_bits(masked, 2 * n))
@@ -197,16 +199,17 @@ def test_rows_written_in_vocabulary_slices(V):
                                rtol=0, atol=1e-5)
 
 
-# (path, keys, queries, r): vocabularies larger than one mixture tile (32768
+# (name, select, keys, queries, r): vocabularies larger than one mixture tile (32768
 # entries on the one-workgroup select and the unsliced split finish, 8192 on
-# the general select), so that rows are written over several tiles.
-LARGE_V_PATHS = [("split-sliced", 40000, 2, 256), ("split-unsliced", 40000, 20, 256),
-                 ("one-workgroup", 40000, 40, 256), ("general-r2048", 40000, 3, 2048)]
+# the sampled and general selects), so that rows are written over several tiles.
+LARGE_V_PATHS = [("split-sliced", "groups", 40000, 2, 256), ("split-unsliced", "parts", 40000, 20, 256),
+                 ("split-400-parts", "parts", 40000, 40, 256), ("one-workgroup", "one-workgroup", 40000, 40, 256),
+                 ("sampled-r2048", "sampled", 40000, 3, 2048), ("general-r2048", "general", 40000, 3, 2048)]
 
 
 @pytest.mark.parametrize("V", [50257, 65536])
-@pytest.mark.parametrize("path,n,B,r", LARGE_V_PATHS, ids=[p[0] for p in LARGE_V_PATHS])
-def test_vocabularies_over_several_tiles(path, n, B, r, V):
+@pytest.mark.parametrize("path,select,n,B,r", LARGE_V_PATHS, ids=[p[0] for p in LARGE_V_PATHS])
+def test_vocabularies_over_several_tiles(path, select, n, B, r, V):
     """Fixed-lambda, RRC and NEST steps with V = 50257 (4-byte mixture) and
     65536 (16-byte mixture): ids and distances bit for bit (integer distances),
     p_M to the usual bound, the decoding outputs on the GPU's own rows; drafts
@@ -222,6 +225,7 @@ def test_vocabularies_over_several_tiles(path, n, B, r, V):
     p_lm = rng.dirichlet(np.ones(V), B).astype(np.float32)
     ko, qo = np.array([0, n]), np.array([0, B])
     prob = _problem(q, k, vals, p_lm, ko, qo, r, 0.05, torch.float32)
+    select_paths.take(prob, select, "fixed", "rrc", "nest")
     o_ids, o_d = oracle.select(q, k, "f32", ko, qo, r)
     p_m, ids, dists = prob.run()
     torch.cuda.synchronize()
@@ -311,6 +315,8 @@ def test_nest_step_synthetic_workloads(name, spec, seed):
     alpha = _median_ratio(w)
     prob = knn.MixtureProblem(w.queries, w.keys, w.values, w.key_offsets, w.query_offsets, w.p_lm, w.r, w.mu,
                               w.lam, key_offsets_host=w.key_offsets_host, query_offsets_host=w.query_offsets_host)
+    if name.endswith("one-workgroup"):
+        select_paths.take(prob, "one-workgroup", "rrc", "nest")
     draft = _drafts(w, seed)
     out = prob.run_nest(alpha, TAU, DELTA, draft_tokens=draft)
     torch.cuda.synchronize()

@@ -140,7 +140,7 @@ SMALL = [
     ("r1", gen.scaled(gen.config("decode_7b"), n_keys=5000, r=1), 9, None),
     ("r4096", gen.scaled(gen.config("decode_7b"), n_keys=9000, r=4096, B=2), 10, None),
     ("planted-bf16", gen.scaled(gen.config("decode_7b"), n_keys=30000, B=3, query_mode="planted"), 12, None),
-    # 40 queries per set, but d is no multiple of 128: the streaming kernel, 8 queries per workgroup
+    # 40 queries per set, but d is no multiple of 128: the several-queries kernel, 16 per workgroup
     ("batch-f16-d1000", gen.scaled(gen.config("specverify_static"), B=80, S=2, n_keys=(3000, 4500), d=1000,
                                    query_mode="iid", mu=1 / math.sqrt(1000)), 14, None),
     ("empty-sets", gen.scaled(gen.config("decode_7b"), B=3, S=5, n_keys=(3000, 2000, 4000, 2500, 1500), d=512,
@@ -171,12 +171,12 @@ def test_small_workloads(name, spec, seed, qps):
         assert ids[:, 0].cpu().numpy().tolist() == w.planted_ids.tolist()
 
 
-@pytest.mark.parametrize("B2", [3, 40])
+@pytest.mark.parametrize("B2", [3, 300])
 def test_empty_key_sets_without_queries(B2):
     """Key sets of 0 keys own no query (a set that owns one needs r keys): one
     between two sets and one at the end, whose offset is the total.  With 2 +
     B2 queries the rows take the split (B2 = 3) or the one-workgroup select
-    (B2 = 40); ids and distances match the oracle bit for bit (integer
+    (B2 = 300, on the smallest workspace); ids and distances match the oracle bit for bit (integer
     distances), p_M to the usual bound."""
     _say(f"empty key sets, {2 + B2} queries")
     rng = np.random.default_rng(31 + B2)
@@ -195,6 +195,7 @@ def test_empty_key_sets_without_queries(B2):
                               torch.as_tensor(vals, device=dev), torch.as_tensor(ko, device=dev),
                               torch.as_tensor(qo, device=dev), torch.as_tensor(p_lm, device=dev), r, 0.1, 0.4,
                               key_offsets_host=ko, query_offsets_host=qo)
+    select_paths.take(prob, "groups" if B2 == 3 else "one-workgroup")
     p_m, ids, dists = prob.run()
     torch.cuda.synchronize()
     o_ids, o_d = oracle.select(q, k, "f32", ko, qo, r)
@@ -386,20 +387,22 @@ def test_mix_entry_point():
 
 def test_split_and_one_workgroup_select_agree():
     """The same queries through the split select (few queries: a 64K-key row
-    over 16 workgroups) and the one-workgroup select (20 queries): the same
-    neighbours and distances bit for bit, p_M within the rounding of the LDS
+    over 16 workgroups) and the one-workgroup select (20 queries on the
+    smallest workspace): the same neighbours and distances bit for bit, p_M within the rounding of the LDS
     atomics.  fp32 keys keep both batches on the streaming distance kernel,
     whose per-query arithmetic does not depend on the batch."""
     _say("split vs one-workgroup select")
     w = gen.make(gen.scaled(gen.config("decode_7b"), B=20, n_keys=65536, d=256, dtype="f32", mu=1 / 16), 29,
                  device="cuda")
-    _, ids20, d20 = _run(w)
-    p20 = _run(w)[0].clone()
-    ids20, d20 = ids20.clone(), d20.clone()
+    all20 = knn.MixtureProblem(w.queries, w.keys, w.values, w.key_offsets, w.query_offsets, w.p_lm, w.r, w.mu, w.lam,
+                               key_offsets_host=w.key_offsets_host, query_offsets_host=w.query_offsets_host)
+    select_paths.take(all20, "one-workgroup")
+    p20, ids20, d20 = all20.run()
     qo = np.array([0, 3], np.int64)
     prob = knn.MixtureProblem(w.queries[:3].contiguous(), w.keys, w.values, w.key_offsets,
                               torch.as_tensor(qo, device="cuda"), w.p_lm[:3].contiguous(), w.r, w.mu, w.lam,
                               key_offsets_host=w.key_offsets_host, query_offsets_host=qo)
+    select_paths.take(prob, "groups")
     p3, ids3, d3 = prob.run()
     torch.cuda.synchronize()
     assert torch.equal(ids3, ids20[:3]) and torch.equal(d3, d20[:3])
@@ -422,9 +425,11 @@ def _sampled_positions(path, n):
 SAMPLED_PATHS = [("parts", 2, 600001), ("groups", 1, 50), ("one-workgroup", 20, 50)]
 
 
-def _check_path(path, B, n, d, r, V):
-    if path != "one-workgroup":
-        assert select_paths.route(B, d, 1, 1, n, B, r, V).select == path
+def _mixture(path, tq, tk, tv, tko, tqo, tp, r, mu, lam):
+    """knn.mixture by the given select (one-workgroup: on the smallest workspace)."""
+    prob = knn.MixtureProblem(tq, tk, tv, tko, tqo, tp, r, mu, lam)
+    select_paths.take(prob, path)
+    return prob.run()
 
 
 @pytest.mark.parametrize("path,B,V", SAMPLED_PATHS, ids=[c[0] for c in SAMPLED_PATHS])
@@ -438,7 +443,6 @@ def test_adversarial_row_takes_the_streamed_path(path, B, V):
     is still exact."""
     _say(f"adversarial sample ({path})")
     n, d, r = 65536, 16, 1000
-    _check_path(path, B, n, d, r, V)
     sampled = _sampled_positions(path, n)
     k = np.zeros((n, d), np.float32)
     k[sampled] = 3.0
@@ -447,7 +451,7 @@ def test_adversarial_row_takes_the_streamed_path(path, B, V):
     p_lm = np.zeros((B, V), np.float32)
     p_lm[:, :50] = 0.02
     tq, tk, tv, tko, tqo, tp = _tensor_inputs(q, k, vals, p_lm, [0, n], [0, B], torch.bfloat16)
-    p_m, ids, dists = knn.mixture(tq, tk, tv, tko, tqo, tp, r, 0.1, 0.5)
+    p_m, ids, dists = _mixture(path, tq, tk, tv, tko, tqo, tp, r, 0.1, 0.5)
     torch.cuda.synchronize()
     expect = np.setdiff1d(np.arange(n), sampled)[:r]
     for b in range(B):
@@ -473,7 +477,6 @@ def test_sample_keeps_fewer_than_r_takes_the_streamed_path(path, B, V):
     every distance exact, so ids and distances equal the oracle's bit for bit."""
     _say(f"sample keeps fewer than r ({path})")
     n, d, r = 65536, 16, 1000
-    _check_path(path, B, n, d, r, V)
     sampled = _sampled_positions(path, n)
     j = np.arange(sampled.size)
     k = np.full((n, d), 100.0, np.float32)
@@ -486,7 +489,7 @@ def test_sample_keeps_fewer_than_r_takes_the_streamed_path(path, B, V):
     p_lm = np.zeros((B, V), np.float32)
     p_lm[:, :50] = 0.02
     tq, tk, tv, tko, tqo, tp = _tensor_inputs(q, k, vals, p_lm, [0, n], [0, B], torch.bfloat16)
-    p_m, ids, dists = knn.mixture(tq, tk, tv, tko, tqo, tp, r, 0.1, 0.5)
+    p_m, ids, dists = _mixture(path, tq, tk, tv, tko, tqo, tp, r, 0.1, 0.5)
     torch.cuda.synchronize()
     qh, dt = oracle.host_elements(tq)
     kh, _ = oracle.host_elements(tk)

@@ -1,9 +1,9 @@
 """GPU parity of relative retrieval confidence (paper Section 3.2, eq. rrc):
 knn_lm_mixture_rrc and knn_mix_rrc against the oracle's rrc_lambda and its
-mixture with one lambda per query, through every select path (split over
-workgroups for few queries, one workgroup per query for rows of at most 64K
-keys, the wide path for longer rows in fine tiles, and the general path for
-the rest: longer rows with r > 2048, or r > 1024)."""
+mixture with one lambda per query, through every select path: split over
+workgroups, wide for long rows in fine tiles, sampled, and, on the smallest
+workspace or with r > 2048, one workgroup per query (the row in registers, or
+streamed)."""
 import math
 
 import numpy as np
@@ -12,6 +12,7 @@ import torch
 
 import oracle
 import parity
+import select_paths
 from workloads import gen
 
 pytestmark = pytest.mark.gpu
@@ -50,17 +51,16 @@ def _integer_case(n, B, seed):
     return q, k, vals, p_lm
 
 
-# (path, n keys, queries, r): the split select needs B * ceil(n / 4096) <= 256,
-# the one-workgroup select n <= 65536 and r <= 1024, the wide one rows of more
-# than 65536 keys in at least 2 r distance tiles with r <= 2048 (16-row tiles
-# here), the general one the rest.
-PATHS = [("split", 40000, 6, 1024), ("one-workgroup", 40000, 40, 1024), ("wide-long-row", 70000, 6, 1024),
-         ("general-long-row", 70000, 6, 2500), ("general-r2048", 40000, 3, 2048), ("split-r1", 5000, 4, 1)]
+# (name, select, n keys, queries, r); one-workgroup and, at r = 2048, general run on the smallest workspace
+PATHS = [("split", "groups", 40000, 6, 1024), ("split-400-parts", "groups", 40000, 40, 1024),
+         ("one-workgroup", "one-workgroup", 40000, 40, 1024), ("wide-long-row", "wide", 70000, 6, 1024),
+         ("general-long-row", "general", 70000, 6, 2500), ("general-r2048", "general", 40000, 3, 2048),
+         ("sampled-r2048", "sampled", 40000, 3, 2048), ("split-r1", "groups", 5000, 4, 1)]
 
 
-@pytest.mark.parametrize("path,n,B,r", PATHS, ids=[p[0] for p in PATHS])
+@pytest.mark.parametrize("path,select,n,B,r", PATHS, ids=[p[0] for p in PATHS])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_rrc_exact_integer_inputs(path, n, B, r, dtype):
+def test_rrc_exact_integer_inputs(path, select, n, B, r, dtype):
     _say(f"rrc exact integers: {path} n={n} B={B} r={r} {dtype}")
     q, k, vals, p_lm = _integer_case(n, B, 40 + r)
     ko, qo = np.array([0, n]), np.array([0, B])
@@ -69,6 +69,7 @@ def test_rrc_exact_integer_inputs(path, n, B, r, dtype):
     prob = knn.MixtureProblem(tq, tk, torch.as_tensor(vals, device=dev), torch.as_tensor(ko, device=dev),
                               torch.as_tensor(qo, device=dev), torch.as_tensor(p_lm, device=dev), r, 0.05,
                               key_offsets_host=ko, query_offsets_host=qo)
+    select_paths.take(prob, select, "rrc")
     p_m, ids, dists, lam = prob.run_rrc(ALPHA, TAU)
     torch.cuda.synchronize()
     o_ids, o_d = oracle.select(q, k, "f32", ko, qo, r)
@@ -144,6 +145,8 @@ def test_rrc_synthetic_workloads(name, spec, seed):
     alpha = float(np.median(ratios))
     prob = knn.MixtureProblem(w.queries, w.keys, w.values, w.key_offsets, w.query_offsets, w.p_lm, w.r, w.mu,
                               w.lam, key_offsets_host=ko, query_offsets_host=qo)
+    if name.endswith("one-workgroup"):
+        select_paths.take(prob, "one-workgroup", "rrc")
     p_m, ids, dists, lam = prob.run_rrc(alpha, TAU)
     torch.cuda.synchronize()
     rep = parity.check_workload(w, p_m, ids, dists, rrc=(alpha, TAU), lambdas=lam)
