@@ -488,9 +488,12 @@ __global__ __launch_bounds__(NW * kWave, 8 / NW) void k_dist_packed(DistArgs a, 
 // 230 us against 193 us; a fragment pass and a norm pass took 370 us).  The
 // loads are cached (both 64-byte halves of a line are used, by two steps;
 // non-temporal they cost 20%), the stores are not.
+//
+// Rows of d = 128 have four steps: of 16, twelve loads go past the row (500,000
+// rows 60 us, 38 us with four; 58 us by the two passes).
 constexpr int kPackSteps = 16;
 
-template <knn_dtype DT, int NW>
+template <knn_dtype DT, int NW, int STEPS = kPackSteps>
 __global__ __launch_bounds__(NW * kWave) void k_pack(const u32x4_t *keys, int64_t n, int64_t d, char *packed) {
     __shared__ float part[kWave];  // each lane's sum so far
     const int lane = threadIdx.x & (kWave - 1);
@@ -505,13 +508,13 @@ __global__ __launch_bounds__(NW * kWave) void k_pack(const u32x4_t *keys, int64_
     u32x4_t *dst = reinterpret_cast<u32x4_t *>(blk) + lane;
     const u32x4_t zero = {0u, 0u, 0u, 0u};
     if (wave == 0) part[lane] = 0.0f;
-    for (int base = 0; base < steps; base += NW * kPackSteps) {
-        const int c0 = base + wave * kPackSteps;
-        u32x4_t v[kPackSteps];
+    for (int base = 0; base < steps; base += NW * STEPS) {
+        const int c0 = base + wave * STEPS;
+        u32x4_t v[STEPS];
 #pragma unroll
-        for (int u = 0; u < kPackSteps; ++u) v[u] = src[4 * (c0 + u < steps ? c0 + u : steps - 1)];
+        for (int u = 0; u < STEPS; ++u) v[u] = src[4 * (c0 + u < steps ? c0 + u : steps - 1)];
 #pragma unroll
-        for (int u = 0; u < kPackSteps; ++u) {
+        for (int u = 0; u < STEPS; ++u) {
             v[u] = in && c0 + u < steps ? v[u] : zero;
             if (c0 + u < steps) __builtin_nontemporal_store(v[u], dst + 64 * (c0 + u));
         }
@@ -523,7 +526,7 @@ __global__ __launch_bounds__(NW * kWave) void k_pack(const u32x4_t *keys, int64_
             if (w == wave) {
                 float p = part[lane];
 #pragma unroll
-                for (int u = 0; u < kPackSteps; ++u) p = dot_vec<DT>(v[u], p);  // steps past the end add zeros
+                for (int u = 0; u < STEPS; ++u) p = dot_vec<DT>(v[u], p);  // steps past the end add zeros
                 part[lane] = p;
             }
         }
@@ -542,6 +545,7 @@ void launch_pack(const u32x4_t *keys, int64_t n, int64_t d, char *packed, int64_
     if (waves >= 8) hipLaunchKernelGGL((k_pack<DT, 8>), grid, dim3(8 * kWave), 0, st, keys, n, d, packed);
     else if (waves >= 4) hipLaunchKernelGGL((k_pack<DT, 4>), grid, dim3(4 * kWave), 0, st, keys, n, d, packed);
     else if (waves >= 2) hipLaunchKernelGGL((k_pack<DT, 2>), grid, dim3(2 * kWave), 0, st, keys, n, d, packed);
+    else if (d == 128) hipLaunchKernelGGL((k_pack<DT, 1, 4>), grid, dim3(kWave), 0, st, keys, n, d, packed);
     else hipLaunchKernelGGL((k_pack<DT, 1>), grid, dim3(kWave), 0, st, keys, n, d, packed);
 }
 

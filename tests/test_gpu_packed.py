@@ -79,11 +79,11 @@ def test_pack_layout(dtype, n, d):
     np.testing.assert_allclose(nr[:n].astype(np.float64), ref, rtol=2e-6, atol=0)
 
 
-# d over the workgroup sizes of the pack kernel (1, 2, 4 and 8 waves of sixteen 32-element steps), whole and
+# d over the workgroup sizes of the pack kernel (1, 2, 4 and 8 waves of sixteen 32-element steps, one of four), whole and
 # with a remainder, and rows that leave the last block partly filled.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("n,d", [(17, 512), (31, 896), (15, 1024), (33, 1152), (18, 2048), (47, 3968), (31, 4096),
-                                 (49, 5248), (16, 8192)])
+@pytest.mark.parametrize("n,d", [(31, 128), (33, 256), (17, 512), (31, 896), (15, 1024), (33, 1152), (18, 2048),
+                                 (47, 3968), (31, 4096), (49, 5248), (16, 8192)])
 def test_pack_wave_splits(dtype, n, d):
     _say(f"pack wave splits {dtype} n={n} d={d}")
     g = torch.Generator(device="cuda").manual_seed(n + d)
