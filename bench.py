@@ -36,8 +36,8 @@ GRAPH_REPLAY = ("tiny", "decode_7b")
 GRAPH_STEPS = 50  # steps captured in one graph
 PMC_FILE = os.path.join(ROOT, "profiles", "dist_kernel_{workload}_pmc.json")
 # The sources the distance kernels are built from (a change makes committed counters stale).
-DIST_SOURCES = ("dist_kernels.hip", "mfma_kernels.hip", "mfma_packed.hip", "mfma_device.h", "knnlm_device.h",
-                "knnlm_internal.h")
+DIST_SOURCES = ("dist_kernels.hip", "dist_multi.hip", "mfma_kernels.hip", "mfma_packed.hip", "mfma_device.h",
+                "tile_rows.h", "knnlm_device.h", "knnlm_internal.h")
 
 
 def _args():

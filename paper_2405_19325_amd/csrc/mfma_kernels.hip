@@ -17,11 +17,12 @@
 // ahead, and one barrier a step orders the buffers.  With the spans staged
 // through registers (two LDS buffers, two to four register sets) a 35-query
 // workgroup ran one wave per SIMD, 98 KiB of LDS and 1.9 us a step; 48 to 72 KiB and
-// 60 to 130 registers let two or three workgroups share a CU.  Measured, before
-// and after, bf16 keys of d = 4096: 8 x 65,536 keys, 16 / 32 / 64 queries 792 / 915 /
-// 1,080 us and 746 / 804 / 905 us (5.75 / 5.35 / 4.75 TB/s); 128 queries on 4 x
-// 65,536 keys of d = 2048: 311 and 306 us.  What is left is the access pattern:
-// 128 bytes of each row at a time stream below the whole-row kernels' 7 TB/s.
+// 60 to 130 registers let two or three workgroups of up to 64 queries share a
+// CU.  Measured, before and after, bf16 keys of d = 4096: 8 x 65,536 keys, 16 / 32
+// / 64 queries 792 / 915 / 1,080 us and 746 / 804 / 905 us (5.75 / 5.35 / 4.75
+// TB/s); 128 queries on 4 x 65,536 keys of d = 2048: 304 and 295 us.  What is left
+// is the access pattern: 128 bytes of each row at a time stream below the
+// whole-row kernels' 7 TB/s.
 //
 // The LDS copy is swizzled -- chunk c (16 bytes) of row n sits at slot n * CH +
 // (c ^ (n % CH)), CH the chunks of a row's span -- so that the fragment reads
